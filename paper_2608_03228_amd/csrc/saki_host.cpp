@@ -1631,7 +1631,9 @@ size_t saki_recall_workspace_bytes(int B, int H_q, int H_kv, int Q, int N_valid,
   if (B <= 0 || H_q <= 0 || H_kv <= 0 || H_q % H_kv != 0 || Q < 0 || N_valid < 0 ||
       d != saki::kHeadDim || k < 1 || k > saki::kMaxK)
     return 0;
-  return saki::recall_plan(B, H_q, H_kv, Q, N_valid).ws_bytes;
+  const size_t ws = saki::recall_plan(B, H_q, H_kv, Q, N_valid).ws_bytes;
+  const saki::OncePlan once = saki::recall_once_plan(B, H_q, H_kv, Q, N_valid);
+  return once.use && once.ws_bytes > ws ? once.ws_bytes : ws;
 }
 
 }  // extern "C"

@@ -150,4 +150,55 @@ inline Plan recall_plan(int B, int H_q, int H_kv, int Q, int N_valid) {
   return p;
 }
 
+// Recall of few rows per key (Q < 16, or a batch whose rows alone do not fill
+// the GPU): the keys of a KV group are read once for all rows of its query
+// heads, 16 nb rows per wave.  Lists of 128 entries (8 bytes) per (row, chunk)
+// from offset 0, which the partial lists of the rows redone by `stream` take
+// over afterwards; a count per (row, chunk), a gate and a redo flag per row.
+struct OncePlan {
+  bool use = false;
+  int nb = 1, row_blocks = 0, chunk = kTile, n_chunks = 1;
+  size_t count_off = 0, tau_off = 0, redo_off = 0, ws_bytes = 0;
+  Plan stream;
+};
+constexpr int kOnceMinChunk = 128;  // keys a wave takes at least
+constexpr int kOnceWaves = 4096;    // waves wanted over the whole GPU
+constexpr int kOnceMaxRows = 2048;  // rows of 16 or more queries a head that take it
+inline OncePlan recall_once_plan(int B, int H_q, int H_kv, int Q, int N_valid) {
+  OncePlan o;
+  const Plan p = recall_plan(B, H_q, H_kv, Q, N_valid);
+  if (N_valid <= 0) return o;
+  // The decision rescores every listed key (0.1 us a row) where the other path
+  // rescores a few: 16 queries over 4,096 keys (512 rows) 59 us against 97,
+  // over 262,144 keys 297 against 1,542; 17,536 rows over 4,096 keys 1,404
+  // against 406.
+  if (p.mfma && (p.n_chunks == 1 || (size_t)B * H_q * Q > (size_t)kOnceMaxRows)) return o;
+  o.stream = make_plan(B, H_q, Q, N_valid, 16, false);
+  const size_t group_rows = (size_t)(H_q / H_kv) * Q, rows = (size_t)B * H_q * Q;
+  o.nb = group_rows > 16 ? 2 : 1;
+  o.row_blocks = (int)((group_rows + 16 * o.nb - 1) / (16 * o.nb));
+  const size_t per_chunk = (size_t)o.row_blocks * B * H_kv, entry = 1024 + sizeof(int);
+  size_t want = (kOnceWaves + per_chunk - 1) / per_chunk;
+  // no more workspace than the rows' other path takes
+  if (p.mfma) {
+    const size_t room = p.ws_bytes / rows > 2 * sizeof(float) ? p.ws_bytes - rows * 2 * sizeof(float) : 0;
+    const size_t most = room > 1024 ? (room - 1024) / (rows * entry) : 0;
+    if (most < 1) return o;
+    if (want > most) want = most;
+  }
+  size_t chunk = round_up(((size_t)N_valid + want - 1) / want, kTile);
+  if (chunk < (size_t)kOnceMinChunk) chunk = kOnceMinChunk;
+  o.chunk = (int)chunk;
+  o.n_chunks = (int)(((size_t)N_valid + chunk - 1) / chunk);
+  size_t lists = rows * o.n_chunks * 1024;
+  if (lists < o.stream.ws_bytes) lists = o.stream.ws_bytes;
+  o.count_off = round_up(lists, 256);
+  o.tau_off = round_up(o.count_off + rows * o.n_chunks * sizeof(int), 256);
+  o.redo_off = round_up(o.tau_off + rows * sizeof(float), 256);
+  o.ws_bytes = round_up(o.redo_off + rows * sizeof(int), 256);
+  if (p.mfma && o.ws_bytes > p.ws_bytes) return o;
+  o.use = true;
+  return o;
+}
+
 }  // namespace saki

@@ -2094,7 +2094,8 @@ __global__ __launch_bounds__(256) void exact_stream_kernel(
     const void* __restrict__ keys, const float* __restrict__ q,
     const int* __restrict__ q_pos, int H_q, int H_kv, int N_cap, int N_valid, int Q,
     int row_blocks, int chunk, int n_chunks, int k, const int* __restrict__ approx,
-    int* __restrict__ hits, int* __restrict__ exact_idx, KeyF64* __restrict__ part) {
+    int* __restrict__ hits, int* __restrict__ exact_idx, KeyF64* __restrict__ part,
+    const int* __restrict__ only) {
   constexpr int D = saki::kHeadDim;
   using KO = KeysF64;
   __shared__ double qsh[kStreamWaves][R][D];
@@ -2108,6 +2109,8 @@ __global__ __launch_bounds__(256) void exact_stream_kernel(
   const int gkv = h / (H_q / H_kv);
   const int row0 = (rb * waves + wave) * R;
   if (row0 >= Q) return;
+  // with `only`, the rows flagged there (a wave with none has nothing to do)
+  if (only && __ballot(lane < R && row0 + lane < Q && only[bh * Q + row0 + lane] != 0) == 0) return;
   int lim[R];
   int kmax = 0;
 #pragma unroll
@@ -2146,7 +2149,7 @@ __global__ __launch_bounds__(256) void exact_stream_kernel(
   for (int r = 0; r < R; ++r) {
     top.finish(r);
     const int i = row0 + r;
-    if (i >= Q) continue;
+    if (i >= Q || (only && only[bh * Q + i] == 0)) continue;
     exact_row_out<KO>(top.entry(r), bh * Q + i, ch, n_chunks, k, approx, hits, exact_idx, part);
   }
 }
@@ -3187,6 +3190,411 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
   if (threadIdx.x == 0) redo[flag] = wg_fallback;
 }
 
+// ---------------------------------------------------------------- exact scores, keys read once
+
+// Exact top-k and recall hits where few rows share many keys (Q < 16, or a
+// batch too small to fill the GPU with one chunk per row).  What bounds it is
+// the key read from HBM, so the rows of all query heads of a KV group share
+// one read: a wave holds 16 of them as MFMA columns (NB times) and streams
+// one chunk of the group's keys.
+//   exact_tau_kernel    per row a gate tau <= the exact k-th score, the least
+//                       float32 lower bound over its candidate list (-inf for
+//                       a list that is not k distinct visible keys)
+//   exact_scan_kernel   bf16x3 scores a3 (error at most E = kExactEps3 ||q|| ||k||,
+//                       as for exact_gate_kernel): every key with
+//                       a3 + E >= tau goes to its (row, chunk) list
+//   exact_decide_kernel float64 scores of a row's listed keys, their top-k
+// A list that fills up (a poor candidate list, or none) raises its own gate:
+// the 64th best listed a3 less the chunk's largest E so far bounds the
+// chunk's 64th exact score from below, and only keys that can still reach it
+// stay.  A list that stays full (many equal scores) or meets a score that is
+// not finite flags its row for exact_stream_kernel.
+// 2^20 float32 keys, 8 KV heads, 32 rows: 13.8 ms as one float64 dot product
+// per (lane, key), which also read the keys once per query head.
+constexpr int kScanCap = 128;        // entries of a (row, chunk) list
+constexpr int kTauWaves = 4;         // rows per work-group of exact_tau_kernel
+struct ScanEntry {
+  float a;  // bf16x3 score
+  int j;
+};
+
+// grid (ceil(rows / kTauWaves)), block 64 * kTauWaves: one wave per row.
+template <bool KBF>
+__global__ __launch_bounds__(kTauWaves * kWave) void exact_tau_kernel(
+    const void* __restrict__ keys, const float* __restrict__ q, const int* __restrict__ q_pos,
+    int H_q, int H_kv, int N_cap, int N_valid, int Q, int k, size_t rows,
+    const int* __restrict__ approx, float* __restrict__ tau, int* __restrict__ redo) {
+  constexpr int D = saki::kHeadDim;
+  const int wave = threadIdx.x / kWave, lane = lane_id();
+  const size_t row = (size_t)blockIdx.x * kTauWaves + wave;
+  if (row >= rows) return;
+  const size_t bh = row / Q;
+  const int i = (int)(row % Q);
+  const int lim = row_limit(i, Q, N_valid, q_pos);
+  const size_t kbase = ((bh / H_q) * H_kv + (bh % H_q) / (H_q / H_kv)) * N_cap;
+  const int aj = lane < k ? approx[row * k + lane] : -1;
+  bool bad = lane < k && (aj < 0 || aj >= lim);
+  uint32_t sorted = lane < k ? (uint32_t)aj : (0x80000000u | (uint32_t)lane);
+  wave_sort<KeysU32>(sorted);
+  const uint32_t nxt = (uint32_t)__shfl_down((int)sorted, 1, kWave);
+  bad |= lane < kWave - 1 && sorted == nxt;
+  if (__ballot(bad) != 0) {
+    if (lane == 0) {
+      tau[row] = -INFINITY;
+      redo[row] = 0;
+    }
+    return;
+  }
+  // eight steps of 8 entries, 8 lanes per entry (dims 16p .. 16p + 15), so that
+  // a float32 sum is at most 12 roundings deep; every load is issued first
+  const int p = lane & 7, slot = lane >> 3;
+  float qv[16];
+  float qs = 0.f;
+  {
+    const float4* qr = reinterpret_cast<const float4*>(q + row * D + 16 * p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float4 v = qr[e];
+      qv[4 * e] = v.x; qv[4 * e + 1] = v.y; qv[4 * e + 2] = v.z; qv[4 * e + 3] = v.w;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) qs = fmaf(qv[e], qv[e], qs);
+  }
+  uint4 w[8][KBF ? 2 : 4];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int e = 8 * u + slot;
+    const int j = __shfl(aj, e, kWave);
+    const size_t off = (kbase + (e < k ? j : 0)) * D + 16 * p;
+#pragma unroll
+    for (int x = 0; x < (KBF ? 2 : 4); ++x)
+      w[u][x] = KBF ? reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(keys) + off)[x]
+                    : reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(keys) + off)[x];
+  }
+  float lo = INFINITY;
+  bool odd = false;  // a bound that is not finite
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    float f[16];
+    constexpr int PE = KBF ? 8 : 4;
+#pragma unroll
+    for (int x = 0; x < (KBF ? 2 : 4); ++x) unpack_piece<KBF>(w[u][x], f + PE * x);
+    float s0 = 0.f, s1 = 0.f, n0 = 0.f, n1 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      s0 = fmaf(qv[e], f[e], s0);
+      s1 = fmaf(qv[e + 1], f[e + 1], s1);
+      n0 = fmaf(f[e], f[e], n0);
+      n1 = fmaf(f[e + 1], f[e + 1], n1);
+    }
+    float sc = s0 + s1, nn = n0 + n1, qq = qs;
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) {
+      sc += xor_shfl_f32(sc, m);
+      nn += xor_shfl_f32(nn, m);
+      qq += xor_shfl_f32(qq, m);
+    }
+    const float b = sc - kTauEps * (1.f + 1e-4f) * sqrtf(qq) * sqrtf(nn);
+    const bool use = 8 * u + slot < k;
+    lo = use ? fminf(lo, b) : lo;
+    odd |= use && !isfinite(b);
+  }
+  lo = wave_min_f32(lo);
+  if (lane == 0) {
+    tau[row] = __ballot(odd) != 0 ? -INFINITY : lo;
+    redo[row] = 0;
+  }
+}
+
+// Rows of a KV group: rho = (query head within the group) * Q + i; a wave takes
+// rows 16 NB rb .. of them and one chunk of keys.  grid: 1-D, xcd_logical_block
+// order over (sequence and KV head, chunk, row block), row blocks fastest (they
+// read the same keys), block 64.
+template <bool KBF, int NB>
+__global__ __launch_bounds__(kWave) void exact_scan_kernel(
+    const void* __restrict__ keys, const float* __restrict__ q, const int* __restrict__ q_pos,
+    int H_q, int H_kv, int N_cap, int N_valid, int Q, int n_bg, int row_blocks, int chunk,
+    int n_chunks, const float* __restrict__ tau, ScanEntry* __restrict__ lists,
+    int* __restrict__ counts, int* __restrict__ redo) {
+  constexpr int D = saki::kHeadDim;
+  const long long lb = xcd_logical_block((long long)row_blocks * n_chunks * n_bg);
+  if (lb < 0) return;
+  const int rb = (int)(lb % row_blocks), ch = (int)((lb / row_blocks) % n_chunks);
+  const size_t bg = (size_t)(lb / ((long long)row_blocks * n_chunks));
+  const int G = H_q / H_kv;
+  const int lane = lane_id(), qi = lane % 16, g = lane / 16;
+  const size_t kbase = bg * N_cap;
+
+  // the wave's rows: query operands (bf16 hi and lo of dims d(kk, g, e), the
+  // order the key loads below use), norm bounds, gates
+  size_t flat[NB];
+  int lim[NB], cnt[NB];
+  float eq[NB], thr[NB];
+  bf16x8_t qh[NB][4], ql[NB][4];
+  int kmax = 0;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int rho = (rb * NB + nb) * kMR + qi;
+    const bool ok = rho < G * Q;
+    const int hh = ok ? rho / Q : 0, i = ok ? rho % Q : 0;
+    flat[nb] = ((bg / H_kv) * H_q + (bg % H_kv) * G + hh) * Q + i;
+    lim[nb] = ok ? row_limit(i, Q, N_valid, q_pos) : 0;
+    kmax = max(kmax, lim[nb]);
+    cnt[nb] = 0;
+    thr[nb] = ok ? tau[flat[nb]] : INFINITY;
+    const float* qr = q + flat[nb] * D;
+    float ss = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const float4 v0 = *reinterpret_cast<const float4*>(qr + 32 * kk + (KBF ? 8 * g : 4 * g));
+      const float4 v1 = *reinterpret_cast<const float4*>(qr + 32 * kk + (KBF ? 8 * g + 4 : 16 + 4 * g));
+      const float f[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+      uint32_t h[4], l[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = f[2 * e], b = f[2 * e + 1];
+        ss = fmaf(a, a, fmaf(b, b, ss));
+        h[e] = bf16x2_bits(a, b);
+        l[e] = bf16x2_bits(a - __uint_as_float(h[e] << 16), b - __uint_as_float(h[e] & 0xffff0000u));
+      }
+      qh[nb][kk] = as_bf16x8(uint4{h[0], h[1], h[2], h[3]});
+      ql[nb][kk] = as_bf16x8(uint4{l[0], l[1], l[2], l[3]});
+    }
+    eq[nb] = kExactEps3 * (1.f + 1e-4f) * sqrtf(sum_lane_groups(ss));
+  }
+  kmax = wave_max_i(kmax);
+  const int kbeg = ch * chunk;
+  const int kend = min(kbeg + chunk, kmax);
+  float emax = 0.f;  // the largest key norm met
+
+  // 16 keys a step: lane (qi, g) loads of key qi the dims 32 kk + 4 g .. + 3 and
+  // 32 kk + 16 + 4 g .. + 3 (float32: 64 contiguous bytes of a key per load) or
+  // 32 kk + 8 g .. + 7 (bf16), clamped to the chunk's last key
+  struct Raw {
+    uint4 v[KBF ? 4 : 8];
+  };
+  auto load = [&](int t0, Raw& r) {
+    const size_t row = kbase + min(t0 + qi, kend - 1);
+#pragma unroll
+    for (int x = 0; x < (KBF ? 4 : 8); ++x)
+      r.v[x] = KBF ? *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(keys) + row * D +
+                                                     32 * x + 8 * g)
+                   : *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(keys) + row * D +
+                                                     16 * x + 4 * g);
+  };
+
+  // row r's list (of column block nb) is full: raise its gate, keep what can
+  // still reach it
+  auto squeeze = [&](int nb, int r) {
+    const int c = __builtin_amdgcn_readlane(cnt[nb], r);
+    const size_t fr = (size_t)readlane_u64((uint64_t)flat[nb], r);
+    ScanEntry* le = lists + (fr * n_chunks + ch) * kScanCap;
+    const float er = readlane_s(eq[nb], r) * emax * (1.f + 1e-4f);
+    __threadfence_block();  // the wave's own entries
+    ScanEntry x = lane < c ? le[lane] : ScanEntry{-INFINITY, 0};
+    ScanEntry y = kWave + lane < c ? le[kWave + lane] : ScanEntry{-INFINITY, 0};
+    const bool odd = (lane < c && !isfinite(x.a)) || (kWave + lane < c && !isfinite(y.a)) || !isfinite(er);
+    uint32_t kx = ord_f32(x.a), ky = ord_f32(y.a);
+    wave_sort<KeysU32>(kx);
+    wave_sort<KeysU32>(ky);
+    wave_merge<KeysU32>(kx, ky);
+    const float gate = unord_f32(readlane_u32(kx, kWave - 1)) - er;
+    const bool tx = lane < c && x.a + er >= gate, ty = kWave + lane < c && y.a + er >= gate;
+    const uint64_t mx = __ballot(tx), my = __ballot(ty);
+    const int n = __popcll(mx) + __popcll(my);
+    const bool full = __ballot(odd) != 0 || n > kScanCap - kMR;
+    __threadfence_block();
+    if (!full) {
+      if (tx) le[prefix_count(mx)] = x;
+      if (ty) le[__popcll(mx) + prefix_count(my)] = y;
+    }
+    if (qi == r) {  // a list that cannot shrink: its row is redone, nothing more is listed
+      thr[nb] = full ? INFINITY : fmaxf(thr[nb], gate);
+      cnt[nb] = full ? kScanCap + 1 : n;
+    }
+    __threadfence_block();
+  };
+
+  auto step = [&](int t0, const Raw& r) {
+    f32x4_t a[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) a[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      uint4 hv, lv;
+      if constexpr (KBF) {
+        hv = r.v[kk];
+        float f[8];
+        unpack_piece<true>(hv, f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss = fmaf(f[e], f[e], ss);
+      } else {
+        float f[8];
+        unpack_piece<false>(r.v[2 * kk], f);
+        unpack_piece<false>(r.v[2 * kk + 1], f + 4);
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = f[2 * e], y = f[2 * e + 1];
+          ss = fmaf(x, x, fmaf(y, y, ss));
+          h[e] = bf16x2_bits(x, y);
+          l[e] = bf16x2_bits(x - __uint_as_float(h[e] << 16), y - __uint_as_float(h[e] & 0xffff0000u));
+        }
+        hv = uint4{h[0], h[1], h[2], h[3]};
+        lv = uint4{l[0], l[1], l[2], l[3]};
+      }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        a[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(hv), qh[nb][kk], a[nb], 0, 0, 0);
+        if constexpr (!KBF)
+          a[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(lv), qh[nb][kk], a[nb], 0, 0, 0);
+        a[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(hv), ql[nb][kk], a[nb], 0, 0, 0);
+      }
+    }
+    // the largest norm of the 16 keys
+    float kn = sum_lane_groups(ss);
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) kn = vmax(kn, xor_shfl_f32(kn, m));
+    kn = sqrtf(kn);
+    emax = vmax(emax, kn);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const float lo = thr[nb] - eq[nb] * kn;
+      uint32_t take = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) take |= (a[nb][v] < lo ? 0u : 1u) << v;  // a score that is not a number is taken
+      if (__ballot(take != 0) == 0) continue;
+      const int j0 = t0 + 4 * g;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (j0 + v >= min(lim[nb], kend)) take &= ~(1u << v);
+      auto offsets = [&](int& pos, int& total) {  // of the row's four lanes
+        const int c = __popc(take);
+        const int c1 = (int)xor_shfl_u32((uint32_t)c, 16), c2 = (int)xor_shfl_u32((uint32_t)c, 32);
+        const int c3 = (int)xor_shfl_u32((uint32_t)c1, 32);
+        pos = g == 1 ? c1 : g == 2 ? c2 + c3 : g == 3 ? c1 + c2 + c3 : 0;
+        total = c + c1 + c2 + c3;
+      };
+      int pos, total;
+      offsets(pos, total);
+      const uint64_t over = __ballot(cnt[nb] + total > kScanCap && cnt[nb] <= kScanCap) & 0xffffull;
+      if (over) {
+        for (uint64_t m = over; m; m &= m - 1) squeeze(nb, __builtin_ctzll(m));
+        const float lo2 = thr[nb] - eq[nb] * kn;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (a[nb][v] < lo2) take &= ~(1u << v);
+        offsets(pos, total);
+      }
+      if (cnt[nb] <= kScanCap) {  // not a row to redo
+        ScanEntry* le = lists + (flat[nb] * n_chunks + ch) * kScanCap + cnt[nb] + pos;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if ((take >> v) & 1u) *le++ = ScanEntry{a[nb][v], j0 + v};
+        cnt[nb] += total;
+      }
+    }
+  };
+
+  // two steps' loads in flight while one is scored
+  if (kbeg < kend) {
+    Raw r[3];
+    load(kbeg, r[0]);
+    load(kbeg + 16, r[1]);
+    for (int t0 = kbeg; t0 < kend; t0 += 48) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int t = t0 + 16 * d;
+        if (t >= kend) break;
+        load(t + 32, r[(d + 2) % 3]);
+        step(t, r[d]);
+      }
+    }
+  }
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+    if (g == 0 && (rb * NB + nb) * kMR + qi < G * Q) {
+      counts[flat[nb] * n_chunks + ch] = min(cnt[nb], kScanCap);
+      if (cnt[nb] > kScanCap) redo[flat[nb]] = 1;  // every chunk that writes it writes 1
+    }
+}
+
+// grid (rows), block 256: the row's listed keys rescored in float64 (four lanes
+// per key, 64 keys a pass) and their top-k.  A round takes up to kDecideKeys
+// keys, the same number at most from each of up to 256 chunks (with 8 chunks
+// and 4 keys from each a round, the rounds' latency made it 35 us).  A row
+// flagged for a redo is left.
+constexpr int kDecideWaves = 4;
+constexpr int kDecideKeys = 1024;
+
+template <bool KBF>
+__global__ __launch_bounds__(kDecideWaves * kWave) void exact_decide_kernel(
+    const void* __restrict__ keys, const float* __restrict__ q, int H_q, int H_kv, int N_cap, int Q,
+    int n_chunks, int k, const ScanEntry* __restrict__ lists, const int* __restrict__ counts,
+    const int* __restrict__ redo, const int* __restrict__ approx, int* __restrict__ hits,
+    int* __restrict__ exact_idx) {
+  constexpr int D = saki::kHeadDim;
+  constexpr int NT = kDecideWaves * kWave;
+  using KD = KeysF64;
+  __shared__ int kj[kDecideKeys];
+  __shared__ double ks[kDecideKeys];
+  __shared__ KeyF64 wl[kDecideWaves][kWave];
+  __shared__ int n_s;
+  const size_t row = blockIdx.x;
+  if (redo[row] != 0) return;  // the whole work-group
+  const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  const size_t bh = row / Q;
+  const size_t kbase = ((bh / H_q) * H_kv + (bh % H_q) / (H_q / H_kv)) * N_cap;
+  const float* qr = q + row * D;
+  KeyF64 best = KD::pad();
+  const int per = kDecideKeys / min(n_chunks, NT);
+  for (int c0 = 0; c0 < n_chunks; c0 += NT) {
+    const int c = c0 + tid;
+    int left = c < n_chunks ? counts[row * n_chunks + c] : 0;
+    const ScanEntry* le = lists + (row * n_chunks + (c < n_chunks ? c : 0)) * kScanCap;
+    for (;;) {
+      __syncthreads();
+      if (tid == 0) n_s = 0;
+      __syncthreads();
+      const int take = min(left, per);
+      if (take > 0) {
+        const int at = atomicAdd(&n_s, take);
+        for (int e = 0; e < take; ++e) kj[at + e] = le[e].j;
+        le += take;
+        left -= take;
+      }
+      __syncthreads();
+      const int n = n_s;  // the same for every thread
+      if (n == 0) break;
+      for (int b = 0; b < n; b += NT / 4) {
+        const int e = b + tid / 4, ec = min(e, n - 1);  // idle quads repeat the last key
+        const double sx = quad_sum_f64(quad_dot_f64<KBF>(keys, kbase + kj[ec], qr, tid & 3));
+        if (e < n && (tid & 3) == 0) ks[e] = sx;
+      }
+      __syncthreads();
+      for (int b = wave * kWave; b < n; b += NT) {
+        const int e = b + lane;
+        // scores of -inf and those that are not numbers are never listed
+        KeyF64 x = e < n && ks[e] > -(double)INFINITY ? KD::make(ks[e], kj[e]) : KD::pad();
+        wave_sort<KD>(x);
+        wave_merge<KD>(best, x);
+      }
+    }
+  }
+  wl[wave][lane] = best;
+  __syncthreads();
+  if (wave != 0) return;
+  for (int w = 1; w < kDecideWaves; ++w) {
+    const KeyF64 b = wl[w][lane];
+    if (KD::gt(KD::readlane(b, 0), KD::readlane(best, kWave - 1))) wave_merge<KD>(best, b);
+  }
+  const int ej = out_index<KD>(best);
+  if (exact_idx && lane < k) exact_idx[row * k + lane] = ej;
+  const int hsum = row_hits(ej, approx, row, k);
+  if (lane == 0) hits[row] = hsum;
+}
+
 // ---------------------------------------------------------------- merge of partials
 
 // grid (rows), block 64 * waves (waves <= kMergeWaves): the waves of a row's
@@ -3719,49 +4127,111 @@ void launch_score(const uint8_t* index, int B, int H_q, int H_kv, int index_head
                        k, top_idx, top_score, nullptr, nullptr);
 }
 
+// Exact float64 scores, one key per lane: all rows, or those flagged in `only`.
+template <bool KBF>
+void launch_exact_stream(const void* keys, const float* q, const int* q_pos, int B, int H_q,
+                         int H_kv, int N_cap, int N_valid, int Q, int k, const int* approx,
+                         int* hits, int* exact_idx, KeyF64* part, const int* only,
+                         const saki::Plan& p, hipStream_t s) {
+  const size_t rows = (size_t)B * H_q * Q;
+  dim3 grid((unsigned)(p.row_blocks * p.n_chunks), B * H_q);
+  dim3 block(kWave * p.waves);
+  if (p.rows == 4)
+    hipLaunchKernelGGL((exact_stream_kernel<KBF, 4>), grid, block, 0, s, keys, q, q_pos, H_q,
+                       H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
+                       hits, exact_idx, part, only);
+  else
+    hipLaunchKernelGGL((exact_stream_kernel<KBF, 1>), grid, block, 0, s, keys, q, q_pos, H_q,
+                       H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
+                       hits, exact_idx, part, only);
+  if (p.n_chunks > 1)
+    hipLaunchKernelGGL((merge_kernel<KeysF64, true>), dim3((unsigned)rows),
+                       dim3(kWave * min(kMergeWaves, p.n_chunks)), 0, s, part, rows, p.n_chunks,
+                       k, exact_idx, nullptr, approx, hits, nullptr, nullptr, only);
+}
+
+// The keys read once for all rows of a KV group: gates, scan, decision, and the
+// rows the scan flagged.
+template <bool KBF, int NB>
+void launch_recall_once(const void* keys, const float* q, const int* q_pos, int B, int H_q,
+                        int H_kv, int N_cap, int N_valid, int Q, int k, const int* approx,
+                        int* hits, int* exact_idx, uint8_t* ws, const saki::OncePlan& p,
+                        hipStream_t s) {
+  const size_t rows = (size_t)B * H_q * Q;
+  ScanEntry* lists = reinterpret_cast<ScanEntry*>(ws);
+  int* counts = reinterpret_cast<int*>(ws + p.count_off);
+  float* tau = reinterpret_cast<float*>(ws + p.tau_off);
+  int* redo = reinterpret_cast<int*>(ws + p.redo_off);
+  // chunks of the plan (which sized the workspace), no more than the GPU holds
+  // waves of at once
+  int chunk = p.chunk, n_chunks = p.n_chunks;
+  const int slots = resident_groups(exact_scan_kernel<KBF, NB>, kWave);
+  const int want = slots > 0 ? max(1, slots / max(1, p.row_blocks * B * H_kv)) : n_chunks;
+  if (want < n_chunks) {
+    chunk = (int)saki::round_up(((size_t)N_valid + want - 1) / want, kTile);
+    n_chunks = (N_valid + chunk - 1) / chunk;
+  }
+  hipLaunchKernelGGL((exact_tau_kernel<KBF>), dim3((unsigned)((rows + kTauWaves - 1) / kTauWaves)),
+                     dim3(kTauWaves * kWave), 0, s, keys, q, q_pos, H_q, H_kv, N_cap, N_valid, Q, k,
+                     rows, approx, tau, redo);
+  const long long total = (long long)p.row_blocks * n_chunks * B * H_kv;
+  hipLaunchKernelGGL((exact_scan_kernel<KBF, NB>), dim3((unsigned)((total + kXcds - 1) / kXcds * kXcds)),
+                     dim3(kWave), 0, s, keys, q, q_pos, H_q, H_kv, N_cap, N_valid, Q, B * H_kv,
+                     p.row_blocks, chunk, n_chunks, (const float*)tau, lists, counts, redo);
+  hipLaunchKernelGGL((exact_decide_kernel<KBF>), dim3((unsigned)rows), dim3(kDecideWaves * kWave), 0,
+                     s, keys, q, H_q, H_kv, N_cap, Q, n_chunks, k, (const ScanEntry*)lists,
+                     (const int*)counts, (const int*)redo, approx, hits, exact_idx);
+  launch_exact_stream<KBF>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx, hits,
+                           exact_idx, reinterpret_cast<KeyF64*>(ws), redo, p.stream, s);
+}
+
 template <bool KBF>
 void launch_recall(const void* keys, const float* q, const int* q_pos, int B, int H_q,
                    int H_kv, int N_cap, int N_valid, int Q, int k, const int* approx,
-                   int* hits, int* exact_idx, uint8_t* ws, const saki::Plan& p,
+                   int* hits, int* exact_idx, uint8_t* ws, size_t ws_bytes, const saki::Plan& p,
                    hipStream_t s) {
+  const saki::OncePlan op = saki::recall_once_plan(B, H_q, H_kv, Q, N_valid);
+  if (op.use && ws && ws_bytes >= op.ws_bytes) {
+    if (op.nb == 2)
+      launch_recall_once<KBF, 2>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx, hits,
+                                 exact_idx, ws, op, s);
+    else
+      launch_recall_once<KBF, 1>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx, hits,
+                                 exact_idx, ws, op, s);
+    return;
+  }
   const size_t rows = (size_t)B * H_q * Q;
   KeyF64* part = p.n_chunks > 1 ? reinterpret_cast<KeyF64*>(ws + p.part_off) : nullptr;
-  dim3 grid((unsigned)(p.row_blocks * p.n_chunks), B * H_q);
-  dim3 block(kWave * p.waves);
-  if (p.mfma) {
-    const int nt_hi = (int)saki::n_tiles(N_valid);
-    uint8_t* khi = ws + p.z_off;
-    uint8_t* klo = khi + (size_t)B * H_kv * nt_hi * kTile * saki::kHeadDim * 2;
-    float* knorm = reinterpret_cast<float*>(ws + p.b_off);
-    // three tiers, each running only the waves the previous one flagged
-    int* flag1 = reinterpret_cast<int*>(ws + p.flag_off);
-    int* flag2 = flag1 + p.flag_count;
-    if (nt_hi > 0)
-      hipLaunchKernelGGL((keys_hi_kernel<KBF>), dim3(nt_hi, B * H_kv), dim3(256), 0, s, keys, N_cap,
-                         N_valid, nt_hi, khi, klo, knorm);
-    {
-      const long long total = (long long)((Q + kMR - 1) / kMR) * p.n_chunks * B * H_q;
-      hipLaunchKernelGGL((exact_gate_kernel<KBF>), dim3((unsigned)(((total + kXcds - 1) / kXcds) * kXcds)),
-                         dim3(kGateWaves * kWave), 0, s, keys, khi, klo, knorm, q, q_pos, H_q, H_kv, N_cap,
-                         N_valid, Q, nt_hi, B * H_q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
-                         hits, exact_idx, part, flag1);
-    }
-    hipLaunchKernelGGL((exact_bf16_kernel<KBF>), xcd_grid(p, B * H_q), block, 0, s, keys, khi,
-                       klo, knorm, q, q_pos, H_q, H_kv, N_cap, N_valid, Q, nt_hi, B * H_q,
-                       p.row_blocks, p.chunk, p.n_chunks, k, approx, hits, exact_idx, part,
-                       (const int*)flag1, flag2);
-    hipLaunchKernelGGL((exact_mfma_kernel<KBF>), xcd_grid(p, B * H_q), block, 0, s, keys, q,
-                       q_pos, H_q, H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k,
-                       approx, hits, exact_idx, part, B * H_q, (const int*)flag2);
-  } else if (p.rows == 4) {
-    hipLaunchKernelGGL((exact_stream_kernel<KBF, 4>), grid, block, 0, s, keys, q, q_pos, H_q,
-                       H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
-                       hits, exact_idx, part);
-  } else {
-    hipLaunchKernelGGL((exact_stream_kernel<KBF, 1>), grid, block, 0, s, keys, q, q_pos, H_q,
-                       H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
-                       hits, exact_idx, part);
+  if (!p.mfma) {  // a workspace of the partial lists alone, or none for a single chunk
+    launch_exact_stream<KBF>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx, hits,
+                             exact_idx, part, nullptr, p, s);
+    return;
   }
+  dim3 block(kWave * p.waves);
+  const int nt_hi = (int)saki::n_tiles(N_valid);
+  uint8_t* khi = ws + p.z_off;
+  uint8_t* klo = khi + (size_t)B * H_kv * nt_hi * kTile * saki::kHeadDim * 2;
+  float* knorm = reinterpret_cast<float*>(ws + p.b_off);
+  // three tiers, each running only the waves the previous one flagged
+  int* flag1 = reinterpret_cast<int*>(ws + p.flag_off);
+  int* flag2 = flag1 + p.flag_count;
+  if (nt_hi > 0)
+    hipLaunchKernelGGL((keys_hi_kernel<KBF>), dim3(nt_hi, B * H_kv), dim3(256), 0, s, keys, N_cap,
+                       N_valid, nt_hi, khi, klo, knorm);
+  {
+    const long long total = (long long)((Q + kMR - 1) / kMR) * p.n_chunks * B * H_q;
+    hipLaunchKernelGGL((exact_gate_kernel<KBF>), dim3((unsigned)(((total + kXcds - 1) / kXcds) * kXcds)),
+                       dim3(kGateWaves * kWave), 0, s, keys, khi, klo, knorm, q, q_pos, H_q, H_kv, N_cap,
+                       N_valid, Q, nt_hi, B * H_q, p.row_blocks, p.chunk, p.n_chunks, k, approx,
+                       hits, exact_idx, part, flag1);
+  }
+  hipLaunchKernelGGL((exact_bf16_kernel<KBF>), xcd_grid(p, B * H_q), block, 0, s, keys, khi,
+                     klo, knorm, q, q_pos, H_q, H_kv, N_cap, N_valid, Q, nt_hi, B * H_q,
+                     p.row_blocks, p.chunk, p.n_chunks, k, approx, hits, exact_idx, part,
+                     (const int*)flag1, flag2);
+  hipLaunchKernelGGL((exact_mfma_kernel<KBF>), xcd_grid(p, B * H_q), block, 0, s, keys, q,
+                     q_pos, H_q, H_kv, N_cap, N_valid, Q, p.row_blocks, p.chunk, p.n_chunks, k,
+                     approx, hits, exact_idx, part, B * H_q, (const int*)flag2);
   if (p.n_chunks > 1)
     hipLaunchKernelGGL((merge_kernel<KeysF64, true>), dim3((unsigned)rows),
                        dim3(kWave * min(kMergeWaves, p.n_chunks)), 0, s, part, rows, p.n_chunks,
@@ -3999,10 +4469,10 @@ int saki_recall(const void* keys, int key_dtype, const float* q, const int* q_po
   uint8_t* w = reinterpret_cast<uint8_t*>(ws);
   if (key_dtype == SAKI_BF16)
     launch_recall<true>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx_idx, hits,
-                        exact_idx, w, p, s);
+                        exact_idx, w, ws_bytes, p, s);
   else
     launch_recall<false>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx_idx, hits,
-                         exact_idx, w, p, s);
+                         exact_idx, w, ws_bytes, p, s);
   return launch_ok() ? SAKI_OK : SAKI_ERR_HIP;
 }
 
