@@ -3959,25 +3959,233 @@ __global__ __launch_bounds__(kAttendWaves * kWave) void attend_kernel(
   out[row * D + lane + HALF] = a1 * il;
 }
 
-template <int RK, bool KBF, int ST, bool RECON>
-void launch_attend(const void* keys, const float* values, const uint8_t* index, int B, int H_q,
-                   int H_kv, int index_heads, int N_cap, int N_valid, const float* q,
-                   const int* q_pos, int Q, const float* Bq, const float* mu, const int* top_idx,
-                   int k, float rope_theta, float* out, hipStream_t s) {
-  dim3 grid((unsigned)Q, (unsigned)(B * H_q));
-  hipLaunchKernelGGL((attend_kernel<RK, KBF, ST, RECON>), grid, dim3(kAttendWaves * kWave), 0, s,
-                     keys, values, index, (int)saki::n_tiles(N_cap), H_q, H_kv, index_heads, N_cap,
-                     N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), out);
+// attend_rows_kernel: the same attention for many rows and exact keys.  A row
+// costs one gather of its listed keys and values (64 KB, from L2) and, with a
+// wave sum and 64 sines and cosines per key, was bound by the VALU (about 90
+// operations per key and wave; 1,147 us for 129,024 rows over 4,096 keys).
+//   - One wave per row, all rows of a work-group's range in turn.  Lane (qi, g)
+//     works on dims 4 qi .. + 3 and 64 + 4 qi .. + 3 (the RoPE pairs stay inside
+//     a lane) of the keys 16 b + 4 g + v, v = 0 .. 3, of step b: 16-byte loads,
+//     a score is a sum over 16 lanes (four DPP adds).
+//   - rope(q, pos) . rope(k, j) depends on pos - j only: per pair it is
+//     cos(t) (q0 k0 + q1 k1) - sin(t) (q1 k0 - q0 k1), t = (pos - j) theta^(-2l/d).
+//     For 0 <= pos - j < 64 n_hi, t = t_hi + t_lo with the sines and cosines of
+//     both in LDS (64 low and n_hi high rows, float32 values rounded from
+//     float64): an angle sum costs four operations.  A step with another
+//     difference evaluates its angles (reduced in float64).
+// The work-groups stay for the whole launch (one per CU, the table takes its
+// LDS), which pays from kAttendManyRows rows on.
+constexpr int kAttendRowWaves = 16;
+constexpr int kRotLo = 64;
+constexpr int kRotRows = 256;          // 128 KiB of LDS
+constexpr int kAttendManyRows = 4096;
+constexpr int kAttendRowsMaxCap = 1 << 22;  // a head's keys within 32-bit byte offsets
+
+// theta^(-2l/d) in quarter turns per position.
+__device__ __forceinline__ double rope_quarter_turns(int l, float log_theta) {
+  constexpr double kTwoOverPi = 0.63661977236758134307553505349006;
+  return exp(-(2.0 * l / saki::kHeadDim) * (double)log_theta) * kTwoOverPi;
+}
+// Sine and cosine of a quarter turns, a in float64: the nearest whole number n
+// of them is taken off exactly, the rest (at most pi / 4) goes through the
+// Taylor series (T: float to x^9 / x^10, double to x^13 / x^14, each below
+// half a float32 step), and n picks the quadrant.
+template <class T>
+__device__ __forceinline__ void rope_sincos_quarters(double a, float* s, float* c) {
+  constexpr double kHalfPi = 1.57079632679489661923132169163975;
+  const double n = rint(a);
+  const T x = (T)((a - n) * kHalfPi), y = x * x;
+  T sp = (T)0, cp = (T)0;
+  if constexpr (sizeof(T) == 8) {
+    sp = fma(y, (T)(1.0 / 6227020800.0), (T)(-1.0 / 39916800.0));
+    sp = fma(y, sp, (T)(1.0 / 362880.0));
+    cp = fma(y, (T)(-1.0 / 87178291200.0), (T)(1.0 / 479001600.0));
+    cp = fma(y, cp, (T)(-1.0 / 3628800.0));
+  } else {
+    sp = (T)(1.0 / 362880.0);
+    cp = (T)(-1.0 / 3628800.0);
+  }
+  sp = fma(y, sp, (T)(-1.0 / 5040.0));
+  sp = fma(y, sp, (T)(1.0 / 120.0));
+  sp = fma(y, sp, (T)(-1.0 / 6.0));
+  sp = fma(y * x, sp, x);
+  cp = fma(y, cp, (T)(1.0 / 40320.0));
+  cp = fma(y, cp, (T)(-1.0 / 720.0));
+  cp = fma(y, cp, (T)(1.0 / 24.0));
+  cp = fma(y, cp, (T)(-0.5));
+  cp = fma(y, cp, (T)1.0);
+  const int m = (int)(n - 4.0 * floor(0.25 * n));  // n mod 4
+  const float sv = (float)((m & 1) ? cp : sp), cv = (float)((m & 1) ? sp : cp);
+  *s = (m & 2) ? -sv : sv;
+  *c = ((m + 1) & 2) ? -cv : cv;
 }
 
-// ---------------------------------------------------------------- dispatch helpers
+// v of lane N of this lane's row of 16
+template <int N>
+__device__ __forceinline__ uint32_t row_bcast_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + N, 0xF, 0xF, false);
+}
+// Sum over the 16 lanes of a row (the same bits in each).
+__device__ __forceinline__ float row_sum_f32(float v) {
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x128, 0xF, 0xF, false));
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x124, 0xF, 0xF, false));
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x122, 0xF, 0xF, false));
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x121, 0xF, 0xF, false));
+  return v;
+}
+// f(i) for i = 0 .. N - 1 as compile-time constants
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
 
-bool launch_ok() { return hipGetLastError() == hipSuccess; }
-
-// 1-D grid for xcd_logical_block: 8 * ceil(total / 8) work-groups.
-dim3 xcd_grid(const saki::Plan& p, int n_bh) {
-  const long long total = (long long)p.row_blocks * p.n_chunks * n_bh;
-  return dim3((unsigned)(((total + kXcds - 1) / kXcds) * kXcds));
+// grid (work-groups resident at once, at most one per 16 rows), block 1024.
+// Work-group w (in XCD order, so that the rows of a KV group meet in one L2)
+// takes rows [w * per_group, (w + 1) * per_group), its waves one each in turn.
+template <bool KBF>
+__global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
+    const void* __restrict__ keys, const float* __restrict__ values, int H_q, int H_kv, int N_cap,
+    int N_valid, const float* __restrict__ q, const int* __restrict__ q_pos, int Q,
+    const int* __restrict__ top_idx, int k, float log_theta, int n_rows, int per_group, int groups,
+    int n_hi, float* __restrict__ out) {
+  constexpr int D = saki::kHeadDim;
+  constexpr int HALF = D / 2;
+  __shared__ __align__(16) float rot[kRotRows][D];  // cosines of pairs 0 .. 63, then sines
+  const long long lg = xcd_logical_block(groups);
+  if (lg < 0) return;  // uniform over the work-group
+  {
+    const int l = threadIdx.x % HALF;
+    const double turn = rope_quarter_turns(l, log_theta);
+    for (int e = threadIdx.x / HALF; e < kRotLo + n_hi; e += kAttendRowWaves * kWave / HALF) {
+      float sn, cs;
+      rope_sincos_quarters<double>((e < kRotLo ? e : (e - kRotLo) * kRotLo) * turn, &sn, &cs);
+      rot[e][l] = cs;
+      rot[e][HALF + l] = sn;
+    }
+  }
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+  const int qi = lane % 16, g = lane / 16;
+  const int r_end = (int)min((long long)n_rows, (lg + 1) * per_group);
+  const int steps = (k + 15) / 16;
+  const int my_e = 16 * (qi >> 2) + 4 * g + (qi & 3);  // this lane's list entry
+  for (int row = (int)(lg * per_group) + wave; row < r_end; row += kAttendRowWaves) {
+    const int bh = row / Q, i = row % Q;
+    const size_t kv = (size_t)(bh / H_q) * H_kv + (bh % H_q) / (H_q / H_kv);
+    const char* kb = reinterpret_cast<const char*>(keys) + kv * N_cap * D * (KBF ? 2 : 4);
+    const char* vb = reinterpret_cast<const char*>(values + kv * N_cap * D);
+    int my_j = my_e < k ? top_idx[(size_t)row * k + my_e] : -1;
+    if (my_j >= N_valid) my_j = -1;  // entries outside [0, N_valid) are skipped
+    const int pos = q_pos ? q_pos[i] : N_valid - 1;
+    const float4 q0 = *reinterpret_cast<const float4*>(q + (size_t)row * D + 4 * qi);
+    const float4 q1 = *reinterpret_cast<const float4*>(q + (size_t)row * D + HALF + 4 * qi);
+    const float qa[4] = {q0.x, q0.y, q0.z, q0.w}, qb[4] = {q1.x, q1.y, q1.z, q1.w};
+    // a skipped entry reads row 0 and gets weight 0
+    const uint32_t j_c = (uint32_t)max(my_j, 0);
+    float my_s = -INFINITY;
+    static_for<4>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if (b >= steps) return;
+      float k0[4][4], k1[4][4];
+      uint32_t jv[4];
+      static_for<4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        jv[v] = row_bcast_u32<4 * b + v>(j_c);
+        if constexpr (KBF) {
+          const uint32_t off = jv[v] * (uint32_t)(D * 2) + (uint32_t)(8 * qi);
+          const uint2 x = *reinterpret_cast<const uint2*>(kb + off);
+          const uint2 y = *reinterpret_cast<const uint2*>(kb + off + D);
+          k0[v][0] = __uint_as_float(x.x << 16); k0[v][1] = __uint_as_float(x.x & 0xffff0000u);
+          k0[v][2] = __uint_as_float(x.y << 16); k0[v][3] = __uint_as_float(x.y & 0xffff0000u);
+          k1[v][0] = __uint_as_float(y.x << 16); k1[v][1] = __uint_as_float(y.x & 0xffff0000u);
+          k1[v][2] = __uint_as_float(y.y << 16); k1[v][3] = __uint_as_float(y.y & 0xffff0000u);
+        } else {
+          const uint32_t off = jv[v] * (uint32_t)(D * 4) + (uint32_t)(16 * qi);
+          const float4 x = *reinterpret_cast<const float4*>(kb + off);
+          const float4 y = *reinterpret_cast<const float4*>(kb + off + HALF * 4);
+          k0[v][0] = x.x; k0[v][1] = x.y; k0[v][2] = x.z; k0[v][3] = x.w;
+          k1[v][0] = y.x; k1[v][1] = y.y; k1[v][2] = y.z; k1[v][3] = y.w;
+        }
+      });
+      float sc[4];
+      const uint32_t reach = (uint32_t)(n_hi * kRotLo);
+      bool far = false;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) far |= (uint32_t)(pos - (int)jv[v]) >= reach;
+      if (__ballot(far) == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const uint32_t dp = (uint32_t)(pos - (int)jv[v]);
+          const float* lo = rot[dp % kRotLo] + 4 * qi;
+          const float* hi = rot[kRotLo + dp / kRotLo] + 4 * qi;
+          const float4 cl4 = *reinterpret_cast<const float4*>(lo), sl4 = *reinterpret_cast<const float4*>(lo + HALF);
+          const float4 ch4 = *reinterpret_cast<const float4*>(hi), sh4 = *reinterpret_cast<const float4*>(hi + HALF);
+          const float cl[4] = {cl4.x, cl4.y, cl4.z, cl4.w}, sl[4] = {sl4.x, sl4.y, sl4.z, sl4.w};
+          const float ch[4] = {ch4.x, ch4.y, ch4.z, ch4.w}, sh[4] = {sh4.x, sh4.y, sh4.z, sh4.w};
+          float acc = 0.f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float cs = fmaf(ch[e], cl[e], -(sh[e] * sl[e])), sn = fmaf(sh[e], cl[e], ch[e] * sl[e]);
+            acc = fmaf(cs, fmaf(qa[e], k0[v][e], qb[e] * k1[v][e]), acc);
+            acc = fmaf(-sn, fmaf(qb[e], k0[v][e], -(qa[e] * k1[v][e])), acc);
+          }
+          sc[v] = row_sum_f32(acc);
+        }
+      } else {
+        double turn[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) turn[e] = rope_quarter_turns(4 * qi + e, log_theta);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double dp = (double)pos - (double)jv[v];
+          float acc = 0.f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float sn, cs;
+            rope_sincos_quarters<float>(dp * turn[e], &sn, &cs);
+            acc = fmaf(cs, fmaf(qa[e], k0[v][e], qb[e] * k1[v][e]), acc);
+            acc = fmaf(-sn, fmaf(qb[e], k0[v][e], -(qa[e] * k1[v][e])), acc);
+          }
+          sc[v] = row_sum_f32(acc);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) my_s = qi == 4 * b + v ? sc[v] : my_s;
+    });
+    // softmax over the row's entries, one per lane
+    my_s = my_j >= 0 ? my_s * (1.f / 11.313708498984761f) : -INFINITY;
+    const float mx = wave_max_f32(my_s);
+    const float p = my_s == -INFINITY ? 0.f : expf(my_s - mx);
+    const float l = wave_sum_f32(p);
+    const float il = l > 0.f ? 1.f / l : 0.f;  // a row without entries writes zeros
+    float o0[4] = {0.f, 0.f, 0.f, 0.f}, o1[4] = {0.f, 0.f, 0.f, 0.f};
+    static_for<4>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if (b >= steps) return;
+      static_for<4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const uint32_t off = row_bcast_u32<4 * b + v>(j_c) * (uint32_t)(D * 4) + (uint32_t)(16 * qi);
+        const float pv = __uint_as_float(row_bcast_u32<4 * b + v>(__float_as_uint(p)));
+        const float4 x = *reinterpret_cast<const float4*>(vb + off);
+        const float4 y = *reinterpret_cast<const float4*>(vb + off + HALF * 4);
+        o0[0] = fmaf(pv, x.x, o0[0]); o0[1] = fmaf(pv, x.y, o0[1]);
+        o0[2] = fmaf(pv, x.z, o0[2]); o0[3] = fmaf(pv, x.w, o0[3]);
+        o1[0] = fmaf(pv, y.x, o1[0]); o1[1] = fmaf(pv, y.y, o1[1]);
+        o1[2] = fmaf(pv, y.z, o1[2]); o1[3] = fmaf(pv, y.w, o1[3]);
+      });
+    });
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o0[e] = sum_lane_groups(o0[e]) * il;
+      o1[e] = sum_lane_groups(o1[e]) * il;
+    }
+    float* op = out + (size_t)row * D + 4 * qi;
+    if (g == 0) *reinterpret_cast<float4*>(op) = float4{o0[0], o0[1], o0[2], o0[3]};
+    if (g == 1) *reinterpret_cast<float4*>(op + HALF) = float4{o1[0], o1[1], o1[2], o1[3]};
+  }
 }
 
 // Work-groups of `kernel` (block `threads`) resident on the whole current
@@ -4004,6 +4212,45 @@ int resident_groups(K kernel, int threads) {
   std::lock_guard<std::mutex> lock(mu);
   cache[key] = cus * per_cu;
   return cus * per_cu;
+}
+
+template <int RK, bool KBF, int ST, bool RECON>
+void launch_attend(const void* keys, const float* values, const uint8_t* index, int B, int H_q,
+                   int H_kv, int index_heads, int N_cap, int N_valid, const float* q,
+                   const int* q_pos, int Q, const float* Bq, const float* mu, const int* top_idx,
+                   int k, float rope_theta, float* out, hipStream_t s) {
+  const size_t rows = (size_t)B * H_q * Q;
+  if constexpr (!RECON) {
+    // 16-byte loads of keys, values, queries and the output; a head's keys
+    // within 32-bit offsets
+    const bool al = ((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(values) |
+                      reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+    const int slots = resident_groups(attend_rows_kernel<KBF>, kAttendRowWaves * kWave);
+    if (al && slots > 0 && rows >= (size_t)kAttendManyRows && rows <= 0x7fffffffu &&
+        N_cap <= kAttendRowsMaxCap) {
+      const int per = std::max(kAttendRowWaves, (int)((rows + slots - 1) / slots));
+      const int groups = (int)((rows + per - 1) / per);
+      const int n_hi = std::min(kRotRows - kRotLo, (N_valid + kRotLo - 1) / kRotLo);
+      hipLaunchKernelGGL((attend_rows_kernel<KBF>), dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)),
+                         dim3(kAttendRowWaves * kWave), 0, s, keys, values, H_q, H_kv, N_cap, N_valid, q,
+                         q_pos, Q, top_idx, k, logf(rope_theta), (int)rows, per, groups, n_hi, out);
+      return;
+    }
+  }
+  dim3 grid((unsigned)Q, (unsigned)(B * H_q));
+  hipLaunchKernelGGL((attend_kernel<RK, KBF, ST, RECON>), grid, dim3(kAttendWaves * kWave), 0, s,
+                     keys, values, index, (int)saki::n_tiles(N_cap), H_q, H_kv, index_heads, N_cap,
+                     N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), out);
+}
+
+// ---------------------------------------------------------------- dispatch helpers
+
+bool launch_ok() { return hipGetLastError() == hipSuccess; }
+
+// 1-D grid for xcd_logical_block: 8 * ceil(total / 8) work-groups.
+dim3 xcd_grid(const saki::Plan& p, int n_bh) {
+  const long long total = (long long)p.row_blocks * p.n_chunks * n_bh;
+  return dim3((unsigned)(((total + kXcds - 1) / kXcds) * kXcds));
 }
 
 template <int RK, bool KBF, int ST>

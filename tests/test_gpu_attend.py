@@ -181,3 +181,35 @@ def test_attend_sequences_groups_short_and_skipped_lists():
                 rows = [1, 2] if (b == 0 and h == 1) else [0, 1, 2]
                 _check(out2[b, h, rows], q[b, h, rows], pos[rows], khat, values[b, g],
                        visible[b, h, rows])
+
+
+@pytest.mark.parametrize("k,N,Q,far,keys_bf16", [(64, 1100, 1030, False, False), (10, 130, 1025, True, True),
+                                                 (33, 64, 1030, True, False)])
+def test_attend_many_rows(k, N, Q, far, keys_bf16):
+    """4,096 rows and more take the kernel with the rotation table: lists of
+    every length up to its four steps, skipped entries, empty rows, and
+    positions whose distance to a key is negative or past the table.  Checked
+    on rows spread over the launch."""
+    rng = np.random.default_rng(k)
+    keys = rng.standard_normal((1, 2, N, 128)).astype(np.float32)
+    if keys_bf16:
+        keys = O.bf16_round(keys).astype(np.float32)
+    values = rng.standard_normal((1, 2, N, 128)).astype(np.float32)
+    q = rng.standard_normal((1, 4, Q, 128)).astype(np.float32)
+    idx = np.stack([rng.permutation(N + 3)[:k] for _ in range(4 * Q)]).reshape(1, 4, Q, k).astype(np.int32)
+    idx[0, :, 5] = -1
+    idx[0, :, 6, 1:] = -1
+    visible = np.where(idx < N, idx, -1)
+    pos = rng.integers(0, N, Q).astype(np.int32)
+    if far:
+        pos[::3] += 40_000
+        pos[1] = -5
+    out = S.saki_attend(_t(values), _t(q), _t(idx, torch.int32), N,
+                        keys=_t(keys, torch.bfloat16 if keys_bf16 else torch.float32),
+                        q_pos=_t(pos, torch.int32)).cpu().numpy()
+    rows = np.unique(np.concatenate([[0, 1, 3, 6, 7, Q - 1], rng.integers(0, Q, 12)]))
+    rows = rows[rows != 5]
+    for h in range(4):
+        assert np.all(out[0, h, 5] == 0.0)
+        _check(out[0, h, rows], q[0, h, rows], pos[rows], keys[0, h // 2], values[0, h // 2],
+               visible[0, h, rows])
