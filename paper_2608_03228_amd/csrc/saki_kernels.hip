@@ -7,7 +7,7 @@
 //                        block maxima and a threshold, then the candidates)
 //   score_scan_kernel    the same in one pass over the codes for long rows
 //                        (batches of decode queries), running top-64 per row
-//   score_stream_kernel  the same for few query rows per code set (decode):
+//   score_decode_kernel  the same for few query rows per code set (decode):
 //                        one key per lane, key range split into chunks
 //   merge_kernel         reduces per-chunk partial top-64 lists of one row
 //   keys_hi_kernel       bf16 hi/lo split of the keys and their norm bounds
@@ -484,53 +484,91 @@ __device__ __forceinline__ bf16x2_t as_bf16x2(uint32_t v) {
   return r;
 }
 
-// ---------------------------------------------------------------- sketch scoring, streaming
+// ---------------------------------------------------------------- sketch scoring, decode
 
-// grid (row_blocks * n_chunks, B * index_heads), block 64*waves.  The rows of
-// a code set are its gq = H_q / index_heads query heads times the Q queries,
-// numbered rho = i * gq + (h % gq) so that one wave's R rows are the heads
-// sharing the codes (for a GQA-shared index) before further queries.  Each
-// wave owns R rows and one key chunk; lane t scores key t of each 64-key tile.
-// With `split` (fewer than four waves' worth of rows per code set) the four
-// waves of a work-group share their R rows and take four consecutive chunks.
-// The query sketch of the rows (Sec. 6: z = B_q^T q, rounded to bf16 for bf16
-// and fp8 codes, and b = q^T mu, float32 sums) is formed before the scan: by
-// the four waves together when they share rows (wave w sums dims 32w ..
-// 32w + 31, the four partial sums are added in wave order), otherwise by
-// each wave for its own rows (dims in order).  The first code tiles are
-// requested before the sketch, so that its loads wait under theirs.
+// Few query rows per code set.  The rows of a code set are its gq = H_q /
+// index_heads query heads times the Q queries, numbered rho = i * gq + (h % gq),
+// so that a work-group's R rows are the heads sharing the codes (for a
+// GQA-shared index) before further queries.  A work-group of W = 8 or 16 waves
+// takes R rows and one chunk of keys, wave w the tiles w, w + W, ... of it, one
+// key of a tile per lane, and leaves one sorted top-64 per row.
+//   sketch  z = B_q^T q (rounded to bf16 for bf16 and fp8 codes) and b = q^T mu
+//           (Sec. 6), float32 sums of 128 / W dims per wave, added in wave
+//           order; the wave's first tiles are requested before.
+//   head    the scores of the wave's first 8 tiles stay in registers.  The 64th
+//           largest of the work-group's 64 W lane maxima is a gate: 64 keys
+//           score at least that, and of the 512 W keys about 67 do.  These go
+//           to the row's candidates.
+//   tail    every further key scoring above the gate is a candidate (the 64
+//           head keys at the gate have lower indices, so ties lose nothing).
+//           After every 16 tiles of a wave, candidates that fill more than half
+//           of their room are cut to the best 64, whose last is the new gate.
+// The candidates (at most decode_cap<R>()) are sorted 64 at a time and merged.  A
+// work-group whose candidates do not fit (many equal scores, scores that rise
+// along the keys) selects online instead, row by row (RowLists).
+// An online top-64 per wave and row (a sort and a merge for every 64 keys
+// that beat the threshold, about 5 in the first 2,048 keys) bound the short
+// chunks: 21 us for 32 rows over 4,001 keys, and 85 us for 4 rows of each of 32
+// fp8 code sets over 100,003 keys (1.2 TB/s).
+constexpr int kDecodeWaves = 16;  // at most
+constexpr int kDecodeTiles = 8;   // head tiles per wave
+constexpr int kDecodeRound = 16;  // tail tiles per wave between checks
+template <int R>
+constexpr int decode_cap() { return R >= 4 ? 512 : 1024; }
+
+// Merges the n sorted lists of 64 at m[(r * stride + i) * 64], i < n, of each
+// row r < R into list 0 of the row, by all waves of the work-group.
+template <class KO, int R>
+__device__ __forceinline__ void merge_tree(typename KO::K* m, int stride, int n, int wave, int waves,
+                                           int lane) {
+  for (int st = 1; st < n; st *= 2) {  // n is uniform over the work-group
+    const int pairs = (n - st + 2 * st - 1) / (2 * st);
+    for (int t = wave; t < R * pairs; t += waves) {
+      typename KO::K* x = m + ((size_t)(t % R) * stride + (size_t)(t / R) * 2 * st) * kWave;
+      typename KO::K a = x[lane];
+      wave_merge<KO>(a, x[(size_t)st * kWave + lane]);
+      x[lane] = a;
+    }
+    __syncthreads();
+  }
+}
+
+// grid: 1-D, xcd_logical_block order over (code set of a sequence, chunk, row
+// group), row groups fastest (they read the same codes), block 1024.
 template <int RK, int ST, int R>
-__global__ __launch_bounds__(256) void score_stream_kernel(
+__global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     const uint8_t* __restrict__ index, int n_tiles, int N_valid, int Q,
     const int* __restrict__ q_pos, const float* __restrict__ q, const float* __restrict__ Bq,
-    const float* __restrict__ mu, int H_q, int H_kv, int gq, int row_blocks, int chunk,
-    int n_chunks, int split, int k, int* __restrict__ top_idx, float* __restrict__ top_score,
+    const float* __restrict__ mu, int H_q, int H_kv, int gq, int n_bi, int row_groups, int chunk,
+    int n_chunks, int k, int* __restrict__ top_idx, float* __restrict__ top_score,
     uint64_t* __restrict__ part) {
   constexpr int ES = code_bytes<ST>();
   constexpr int CPP = saki::kChunkBytes / ES;
   constexpr int NP = RK / CPP;
   constexpr size_t TB = (size_t)kTile * RK * ES;
   using KO = KeysF32;
+  using K = KO::K;
   constexpr int D = saki::kHeadDim;
+  constexpr int WM = kDecodeWaves, T = kDecodeTiles, CAP = decode_cap<R>();
   constexpr int NO = R * (RK + 1);  // sketch outputs of R rows
-  __shared__ float zs[kStreamWaves][R][RK + 1];  // element RK: the mean term b
-  __shared__ float zpart[kStreamWaves][NO];      // split: partial sums of wave w
-  __shared__ uint64_t lmem[kStreamWaves][R][kList];
-  __shared__ uint64_t bmem[kStreamWaves][R][kList];
-  // the wave index is uniform over the wave: say so, so that what depends on
-  // it (the sketch's dim slice, the chunk) stays in scalar registers
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-  const int waves = blockDim.x / kWave;
-  const int rb = blockIdx.x % row_blocks;
-  const int ch = split ? (blockIdx.x / row_blocks) * waves + wave : blockIdx.x / row_blocks;
-  const size_t bi = blockIdx.y;  // b * index_heads + code set
+  constexpr size_t kPartB = (size_t)WM * NO * 4, kMaxB = (size_t)R * WM * kWave * 4, kRowB = (size_t)WM * kWave * 16;
+  constexpr size_t kArea = kPartB > kMaxB ? (kPartB > kRowB ? kPartB : kRowB) : (kMaxB > kRowB ? kMaxB : kRowB);
+  __shared__ __align__(16) uint8_t area[kArea];  // sketch parts, lane maxima, online lists
+  __shared__ float zs[R][RK + 1];                // element RK: the mean term b
+  __shared__ __align__(16) uint32_t zw[R][RK / 2];  // pairs of bf16 elements
+  __shared__ K buf[R][CAP];
+  __shared__ int cnt[R];
+  const int tid = threadIdx.x, W = blockDim.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
+  const long long lb = xcd_logical_block((long long)row_groups * n_chunks * n_bi);
+  if (lb < 0) return;  // the whole work-group
+  const int rg = (int)(lb % row_groups), ch = (int)((lb / row_groups) % n_chunks);
+  const size_t bi = (size_t)(lb / ((long long)row_groups * n_chunks));  // b * index_heads + code set
   const int index_heads = H_q / gq;
   const size_t b = bi / index_heads;
   const int ih = (int)(bi % index_heads);
   const int n_rho = gq * Q;
-  const int row0 = split ? rb * R : (rb * waves + wave) * R;
-  if (row0 >= n_rho) return;  // never with split (row_blocks = ceil(n_rho / R))
-
+  const int row0 = rg * R;
   int lim[R];
   size_t flat[R];  // (b * H_q + h) * Q + i of each row
   int kmax = 0;
@@ -539,191 +577,265 @@ __global__ __launch_bounds__(256) void score_stream_kernel(
     const int rho = row0 + r;
     const bool ok = rho < n_rho;
     const int i = ok ? rho / gq : 0;
-    const int h = ih * gq + (ok ? rho % gq : 0);
-    flat[r] = (b * H_q + h) * Q + i;
+    flat[r] = (b * H_q + ih * gq + (ok ? rho % gq : 0)) * Q + i;
     lim[r] = ok ? row_limit(i, Q, N_valid, q_pos) : 0;
-    kmax = lim[r] > kmax ? lim[r] : kmax;
+    kmax = max(kmax, lim[r]);
   }
-  RowLists<KO, R> top;
-  top.init(&lmem[wave][0][0], &bmem[wave][0][0]);
-
   const int kbeg = ch * chunk;
   const int kend = min(kbeg + chunk, kmax);
   const uint8_t* hbase = index + bi * n_tiles * TB;
-  // the next tile's pieces are loaded before this tile is scored (sketches of
-  // up to 128 bytes per key; wider ones are loaded as they are used)
-  constexpr int PF = NP <= 8 ? NP : 1;
-  uint4 nxt[PF];
-  auto load_tile = [&](int t0, uint4* v) {
-    const uint8_t* tb = hbase + (size_t)(t0 / kTile) * TB + (size_t)lane * 16;
-#pragma unroll
-    for (int p = 0; p < PF; ++p) v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)p * kTile * 16);
+  // a tile's pieces are loaded two tiles ahead of their use (up to 64 bytes per
+  // key, 128 where the registers allow; wider codes are loaded as they are used)
+  constexpr int ZW = ST == kStF32 ? RK : RK / 2;  // words of a row's z
+  constexpr bool kScalarZ = R * ZW <= 64;
+  constexpr int PF = kScalarZ && (NP <= 4 || (NP <= 8 && R == 1 && ST != kStFp8)) ? NP : 0;
+  struct Raw {
+    uint4 v[PF ? PF : 1];
   };
-  // with at most 32 bytes of bf16 or fp8 code per key, two tiles are loaded
-  // ahead (into two buffers taken in turn) so that as many bytes are in
-  // flight as for wider codes; otherwise one
-  constexpr int kAhead = ST != kStF32 && NP * 16 <= 32 ? 2 : 1;
-  uint4 nxt2[PF];
-  if (kbeg < kend) load_tile(kbeg, nxt);
-  if (kAhead == 2 && kbeg + kTile < kend) load_tile(kbeg + kTile, nxt2);
-  // the query sketch: output o = r * (RK + 1) + m of the rows in lane o % 64
-  // (m < RK: z_m, m = RK: b), loads taken 16 dims at a time
-  if (split) {
-    constexpr int DS = D / kStreamWaves;
-    static_assert(DS % 16 == 0, "dim slices of whole load groups");
+  auto tile_ptr = [&](int t0) { return hbase + (size_t)(t0 / kTile) * TB + (size_t)lane * 16; };
+  auto load = [&](int t0, Raw& x) {
+    if constexpr (PF > 0) {
+      if (t0 >= kend) return;
+      const uint8_t* tb = tile_ptr(t0);
+#pragma unroll
+      for (int p = 0; p < PF; ++p) x.v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)p * kTile * 16);
+    }
+  };
+  const int t_first = kbeg + wave * kTile;
+  Raw ra, rb;
+  load(t_first, ra);
+  load(t_first + W * kTile, rb);
+
+  // ---- the query sketch
+  {
+    constexpr int DB = D / WM;  // dims loaded at a time
+    const int DS = D / W;
+    float* zpart = reinterpret_cast<float*>(area);
     for (int o0 = 0; o0 < NO; o0 += kWave) {
-      const int o = o0 + lane;
-      const int r = R == 1 ? 0 : min(o / (RK + 1), R - 1), m = o % (RK + 1);
-      const int rho = row0 + r;
-      const bool rv = rho < n_rho;
-      const int i = rv ? rho / gq : 0;
-      const int h = ih * gq + (rv ? rho % gq : 0);
+      const int o = min(o0 + lane, NO - 1);
+      const int r = R == 1 ? 0 : o / (RK + 1), m = o % (RK + 1);
+      const int rho = min(row0 + r, n_rho - 1);
+      const int h = ih * gq + rho % gq;
       const int stride = m < RK ? RK : 1;
-      const float* qv = q + ((b * H_q + h) * Q + i) * D + wave * DS;
+      const float* qv = q + ((b * H_q + h) * Q + rho / gq) * D + wave * DS;
       const float* col = (m < RK ? Bq + (size_t)h * D * RK + m : mu + (size_t)(h / (H_q / H_kv)) * D) +
                          (size_t)wave * DS * stride;
       float acc = 0.f;
-#pragma unroll 1
-      for (int c0 = 0; c0 < DS; c0 += 16) {
-        float qa[16], ba[16];
+      for (int c0 = 0; c0 < DS; c0 += DB) {
+        float qa[DB], ba[DB];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < DB; ++u) {
           qa[u] = qv[c0 + u];
           ba[u] = col[(size_t)(c0 + u) * stride];
         }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) acc = fmaf(qa[u], ba[u], acc);
+        for (int u = 0; u < DB; ++u) acc = fmaf(qa[u], ba[u], acc);
       }
-      if (o < NO) zpart[wave][o] = acc;
+      zpart[wave * NO + o] = acc;
+    }
+    if (tid < R) cnt[tid] = 0;
+    __syncthreads();
+    for (int o = tid; o < NO; o += W * kWave) {
+      float v = zpart[o];
+      for (int w = 1; w < W; ++w) v += zpart[w * NO + o];
+      const int r = o / (RK + 1), m = o % (RK + 1);
+      zs[r][m] = ST != kStF32 && m < RK ? bf16_round(v) : v;
     }
     __syncthreads();
-    for (int o = lane; o < NO; o += kWave) {
-      const int r = o / (RK + 1), m = o % (RK + 1);
-      float v = ((zpart[0][o] + zpart[1][o]) + zpart[2][o]) + zpart[3][o];
-      if (ST != kStF32 && m < RK) v = bf16_round(v);
-      zs[wave][r][m] = row0 + r < n_rho ? v : 0.f;
-    }
-    wave_lds_sync();
-  } else {
-    constexpr int CG = 16;
-    for (int o0 = 0; o0 < NO; o0 += kWave) {
-      const int o = o0 + lane;
-      // with one row per wave the query row is the same in every lane
-      const int r = R == 1 ? 0 : min(o / (RK + 1), R - 1), m = o % (RK + 1);
-      const int rho = row0 + r;
-      const bool rv = rho < n_rho;
-      const bool ok = o < NO && rv;
-      const int i = rv ? rho / gq : 0;
-      const int h = ih * gq + (rv ? rho % gq : 0);
-      const float* qv = q + ((b * H_q + h) * Q + i) * D;
-      const float* col = m < RK ? Bq + (size_t)h * D * RK + m : mu + (size_t)(h / (H_q / H_kv)) * D;
-      const int stride = m < RK ? RK : 1;
-      float acc = 0.f;
-#pragma unroll 1
-      for (int c0 = 0; c0 < D; c0 += CG) {
-        float qa[CG], ba[CG];
-#pragma unroll
-        for (int u = 0; u < CG; ++u) {
-          qa[u] = qv[c0 + u];
-          ba[u] = col[(size_t)(c0 + u) * stride];
-        }
-#pragma unroll
-        for (int u = 0; u < CG; ++u) acc = fmaf(qa[u], ba[u], acc);
-      }
-      if (ST != kStF32 && m < RK) acc = bf16_round(acc);
-      if (o < NO) zs[wave][r][m] = ok ? acc : 0.f;
-    }
-    wave_lds_sync();
   }
-  float bb[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) bb[r] = zs[wave][r][RK];
-  if constexpr (ST != kStF32) {
-    // bf16 codes: each 32-bit word holds elements (2e, 2e + 1), scored with
-    // the packed bf16 dot product against the query sketch's pairs; fp8
-    // codes are first widened to such words (exactly)
-    // the pairs are the same in every lane: when they fit, scalar registers
-    // hold them and the vector registers are left to the key tiles
-    constexpr bool kScalarZ = R * RK / 2 <= 64;
-    uint32_t zp[R][RK / 2];
+  // z (as pairs for bf16 and fp8 codes) in scalar registers when it fits (it is
+  // the same in every lane), else read from LDS with the pieces
+  uint32_t zp[kScalarZ ? R : 1][kScalarZ ? ZW : 1];
+  if constexpr (ST == kStF32 && kScalarZ) {
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int m = 0; m < RK / 2; ++m) {
-        const uint32_t v = (__float_as_uint(zs[wave][r][2 * m]) >> 16) |
-                           (__float_as_uint(zs[wave][r][2 * m + 1]) & 0xffff0000u);
-        zp[r][m] = kScalarZ ? (uint32_t)__builtin_amdgcn_readfirstlane((int)v) : v;
-      }
-    // one tile: the words of bf16 pairs from `cur` (and the pieces not
-    // prefetched), then `refill` (which may reload cur's registers), then the
-    // dot products
-    auto tile = [&](int t0, const uint4* cur, auto&& refill) {
-      const int j = t0 + lane;
-      const uint8_t* tb = hbase + (size_t)(t0 / kTile) * TB;
-      uint32_t w[RK / 2];
-      auto put = [&](int p, const uint4& v) {  // piece p -> its words of bf16 pairs
+      for (int m = 0; m < RK; ++m)
+        zp[r][m] = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(zs[r][m]));
+  } else if constexpr (ST != kStF32) {
+    auto pair = [&](int r, int m) {
+      return (__float_as_uint(zs[r][2 * m]) >> 16) | (__float_as_uint(zs[r][2 * m + 1]) & 0xffff0000u);
+    };
+    if constexpr (kScalarZ) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int m = 0; m < RK / 2; ++m)
+          zp[r][m] = (uint32_t)__builtin_amdgcn_readfirstlane((int)pair(r, m));
+    } else {
+      for (int o = tid; o < R * RK / 2; o += W * kWave) zw[o / (RK / 2)][o % (RK / 2)] = pair(o / (RK / 2), o % (RK / 2));
+      __syncthreads();
+    }
+  }
+  float bb[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) bb[r] = zs[r][RK];
+
+  // scores of this lane's key of tile t0 (-inf past a row's limit)
+  auto score = [&](int t0, const Raw& x, float* out) {
+    float acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.f;
+    auto piece = [&](int p, const uint4& v) {
+      if constexpr (ST == kStF32) {
+        const float c[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[r] = fmaf(kScalarZ ? __uint_as_float(zp[kScalarZ ? r : 0][kScalarZ ? 4 * p + e : 0]) : zs[r][4 * p + e],
+                          c[e], acc[r]);
+      } else {
+        constexpr int WP = CPP / 2;  // words of bf16 pairs
+        uint32_t w[WP];
+        const uint32_t vv[4] = {v.x, v.y, v.z, v.w};
         if constexpr (ST == kStFp8) {
-          const uint32_t vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const uint2 bw = e4m3x4_to_bf16(vv[e]);
-            w[8 * p + 2 * e] = bw.x;
-            w[8 * p + 2 * e + 1] = bw.y;
+            w[2 * e] = bw.x;
+            w[2 * e + 1] = bw.y;
           }
         } else {
-          w[4 * p] = v.x; w[4 * p + 1] = v.y; w[4 * p + 2] = v.z; w[4 * p + 3] = v.w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = vv[e];
         }
-      };
 #pragma unroll
-      for (int p = 0; p < PF; ++p) put(p, cur[p]);
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int p = PF; p < NP; ++p)
-        put(p, *reinterpret_cast<const uint4*>(tb + (size_t)p * kTile * 16 + (size_t)lane * 16));
-      refill();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float acc = 0.f;
-#pragma unroll
-        for (int m = 0; m < RK / 2; ++m) acc = __builtin_amdgcn_fdot2_f32_bf16(as_bf16x2(w[m]), as_bf16x2(zp[r][m]), acc, false);
-        top.offer(r, j < lim[r] ? acc + bb[r] : -INFINITY, j);
+          for (int e = 0; e < WP; ++e) {
+            const uint32_t z = kScalarZ ? zp[kScalarZ ? r : 0][kScalarZ ? WP * p + e : 0] : zw[r][WP * p + e];
+            acc[r] = __builtin_amdgcn_fdot2_f32_bf16(as_bf16x2(w[e]), as_bf16x2(z), acc[r], false);
+          }
       }
     };
-    if constexpr (kAhead == 2) {
-      for (int t0 = kbeg; t0 < kend; t0 += 2 * kTile) {
-        tile(t0, nxt, [&] { if (t0 + 2 * kTile < kend) load_tile(t0 + 2 * kTile, nxt); });
-        if (t0 + kTile >= kend) break;
-        tile(t0 + kTile, nxt2, [&] { if (t0 + 3 * kTile < kend) load_tile(t0 + 3 * kTile, nxt2); });
-      }
+    if constexpr (PF > 0) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) piece(p, x.v[p]);
     } else {
-      for (int t0 = kbeg; t0 < kend; t0 += kTile)
-        tile(t0, nxt, [&] { if (t0 + kTile < kend) load_tile(t0 + kTile, nxt); });
+      // pieces at a time: with z from LDS, at most 64 registers of it and at
+      // least two rounds (a loop that is not unrolled, so that z is not kept)
+      constexpr int PZ = std::min(64 / (R * (ST == kStFp8 ? 8 : 4)), NP / 2);
+      constexpr int PB = kScalarZ ? std::min(NP, 8) : std::max(PZ, 1);
+      const uint8_t* tb = tile_ptr(t0);
+      auto batch = [&](int p0) {
+        uint4 v[PB];
+#pragma unroll
+        for (int p = 0; p < PB; ++p) v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)(p0 + p) * kTile * 16);
+#pragma unroll
+        for (int p = 0; p < PB; ++p) piece(p0 + p, v[p]);
+      };
+      if constexpr (kScalarZ) {
+#pragma unroll
+        for (int p0 = 0; p0 < NP; p0 += PB) batch(p0);
+      } else {
+#pragma unroll 1
+        for (int p0 = 0; p0 < NP; p0 += PB) batch(p0);
+      }
     }
-  } else {
-    for (int t0 = kbeg; t0 < kend; t0 += kTile) {
-      const int j = t0 + lane;
-      const uint8_t* tb = hbase + (size_t)(t0 / kTile) * TB;
-      float c[RK];
+    const int j = t0 + lane;
 #pragma unroll
-      for (int p = 0; p < PF; ++p) unpack_codes<ST>(nxt[p], c + p * CPP);
+    for (int r = 0; r < R; ++r) out[r] = j < lim[r] ? acc[r] + bb[r] : -INFINITY;
+  };
+  auto append = [&](int r, bool take, float sv, int j) {
+    const uint64_t mask = __ballot(take);
+    if (mask == 0) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&cnt[r], __popcll(mask));
+    at = __builtin_amdgcn_readfirstlane(at) + prefix_count(mask);
+    if (take && at < CAP) buf[r][at] = KO::make(sv, j);
+  };
+
+  // ---- the head
+  float s[T][R];
 #pragma unroll
-      for (int p = PF; p < NP; ++p) {
-        const uint4 v = *reinterpret_cast<const uint4*>(tb + (size_t)p * kTile * 16 + (size_t)lane * 16);
-        unpack_codes<ST>(v, c + p * CPP);
-      }
-      if (t0 + kTile < kend) load_tile(t0 + kTile, nxt);
+  for (int i = 0; i < T; ++i) {
+    const int t0 = t_first + i * W * kTile;
+    if (t0 < kend) {
+      score(t0, (i & 1) ? rb : ra, s[i]);
+      load(t0 + 2 * W * kTile, (i & 1) ? rb : ra);
+    } else {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float acc = 0.f;
-#pragma unroll
-        for (int m = 0; m < RK; ++m) acc = fmaf(zs[wave][r][m], c[m], acc);
-        top.offer(r, j < lim[r] ? acc + bb[r] : -INFINITY, j);
-      }
+      for (int r = 0; r < R; ++r) s[i][r] = -INFINITY;
     }
   }
+  float thr[R];  // the gate (-inf: every key is a candidate)
+#pragma unroll
+  for (int r = 0; r < R; ++r) thr[r] = -INFINITY;
+  if (kend - kbeg > CAP) {
+    uint32_t* mx = reinterpret_cast<uint32_t*>(area);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float m = s[0][r];
+#pragma unroll
+      for (int i = 1; i < T; ++i) m = fmaxf(m, s[i][r]);
+      uint32_t o = ord_f32(m);
+      wave_sort<KeysU32>(o);
+      mx[(r * W + wave) * kWave + lane] = o;
+    }
+    __syncthreads();
+    merge_tree<KeysU32, R>(mx, W, W, wave, W, lane);
+#pragma unroll
+    for (int r = 0; r < R; ++r) thr[r] = unord_f32(mx[r * W * kWave + kWave - 1]);
+  }
+#pragma unroll
   for (int r = 0; r < R; ++r) {
-    top.finish(r);
-    if (row0 + r >= n_rho || ch >= n_chunks) continue;  // a split wave past the last chunk
-    const uint64_t e = top.entry(r);
+    // at or above the gate: above the next float below it; scores of -inf never
+    const float below = thr[r] == -INFINITY ? -INFINITY : unord_f32(ord_f32(thr[r]) - 1u);
+#pragma unroll
+    for (int i = 0; i < T; ++i) append(r, s[i][r] > below, s[i][r], t_first + i * W * kTile + lane);
+  }
+
+  // ---- the tail
+  auto tail = [&](int t0, Raw& x) {
+    float v[R];
+    score(t0, x, v);
+    load(t0 + 2 * W * kTile, x);
+#pragma unroll
+    for (int r = 0; r < R; ++r) append(r, v[r] > thr[r], v[r], t0 + lane);
+  };
+  // the row's candidates -> sorted, the best 64 first (every wave takes part)
+  auto most_candidates = [&]() {
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) n = max(n, cnt[r]);
+    return n;
+  };
+  auto sort_candidates = [&](int most) {
+    const int segs = max(1, (most + kWave - 1) / kWave);
+    for (int t = wave; t < R * segs; t += W) {
+      const int r = t % R, at = (t / R) * kWave + lane;
+      K x = at < cnt[r] ? buf[r][at] : KO::pad();
+      wave_sort<KO>(x);
+      buf[r][at] = x;
+    }
+    __syncthreads();
+    merge_tree<KO, R>(&buf[0][0], CAP / kWave, segs, wave, W, lane);
+  };
+  const int head = W * T * kTile, round = W * kDecodeRound * kTile;
+  for (int r0 = kbeg + head; r0 < kend; r0 += round) {
+    for (int t0 = r0 + wave * kTile; t0 < min(kend, r0 + round); t0 += 2 * W * kTile) {
+      tail(t0, ra);
+      if (t0 + W * kTile < kend) tail(t0 + W * kTile, rb);
+    }
+    if (r0 + round >= kend) break;
+    __syncthreads();
+    const int most = most_candidates();
+    if (most > CAP) break;
+    if (most > CAP / 2) {
+      sort_candidates(most);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (cnt[r] >= kWave) thr[r] = fmaxf(thr[r], KO::score(buf[r][kWave - 1]));
+      __syncthreads();  // every wave has read the counts
+      if (tid < R) cnt[tid] = min(cnt[tid], kWave);
+    }
+    __syncthreads();  // before the next round's candidates
+  }
+  __syncthreads();
+
+  auto out_row = [&](int r, K e) {
+    if (row0 + r >= n_rho) return;
     if (n_chunks == 1) {
       if (lane < k) {
         const size_t o = flat[r] * k + lane;
@@ -733,6 +845,37 @@ __global__ __launch_bounds__(256) void score_stream_kernel(
     } else {
       part[(flat[r] * n_chunks + ch) * kMaxK + lane] = e;
     }
+  };
+  const int most = most_candidates();
+  if (most <= CAP) {
+    sort_candidates(most);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (wave == r) out_row(r, buf[r][lane]);
+    return;
+  }
+  // ---- too many candidates: an online top-64 per wave, row by row
+  K* lists = reinterpret_cast<K*>(area);  // [W][64], then the waves' buffers [W][64]
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    __syncthreads();
+    RowLists<KO, 1> top;
+    top.init(lists + wave * kWave, lists + (W + wave) * kWave);
+    for (int t0 = t_first; t0 < kend; t0 += W * kTile) {
+      float v[R];
+      load(t0, ra);
+      score(t0, ra, v);
+      float sv = v[0];
+#pragma unroll
+      for (int x = 1; x < R; ++x) sv = x == r ? v[x] : sv;
+      top.offer(0, sv, t0 + lane);
+    }
+    top.finish(0);
+    __syncthreads();
+    merge_tree<KO, 1>(lists, W, W, wave, W, lane);
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+      if (x == r && wave == 0) out_row(x, lists[lane]);
   }
 }
 
@@ -4299,6 +4442,51 @@ saki::Plan one_round(saki::Plan p, K kernel, int groups_per_chunk, int chunks_pe
   return p;
 }
 
+// Rows of up to kDecodeOne keys are one chunk (16 tiles a wave take about as
+// long as the merge launch that two chunks would need).  Longer ones are cut so
+// that the work-groups fill the GPU once, at least kDecodeMin keys each, in no
+// more chunks than the plan (which sized the workspace) has.  Work-groups have
+// 16 waves (fewer lists: 4 rows of each of 32 fp8 code sets over 100,003 keys
+// 43 us, with 8 waves 49), or 8 where 16 would leave chunks of more than
+// kDecodeLong keys (streaming counts then, and the waits of several small
+// work-groups at their barriers overlap: 32 rows over 2^20 keys 360 us, with
+// 16 waves 376).
+constexpr int kDecodeOne = 16384;
+constexpr int kDecodeMin = 4096;
+constexpr int kDecodeLong = 32768;
+template <int RK, int ST, int R>
+void launch_decode(const uint8_t* index, int nt, int B, int H_q, int H_kv, int gq, int N_valid,
+                   const float* q, const int* q_pos, int Q, const float* Bq, const float* mu, int k,
+                   int* top_idx, float* top_score, uint8_t* ws, const saki::Plan& p0, hipStream_t s) {
+  const int n_bi = B * (H_q / gq), row_groups = (gq * Q + R - 1) / R;
+  const size_t rows = (size_t)B * H_q * Q, n = N_valid > 0 ? (size_t)N_valid : 1;
+  int threads = kDecodeWaves * kWave;
+  size_t want = 1;
+  if (n > (size_t)kDecodeOne) {
+    auto chunks = [&] {
+      const long long slots = resident_groups(score_decode_kernel<RK, ST, R>, threads);
+      return (size_t)std::max(1LL, slots / ((long long)row_groups * n_bi));
+    };
+    want = chunks();
+    if (n / want > (size_t)kDecodeLong) {
+      threads /= 2;
+      want = chunks();
+    }
+    want = std::min({want, (n + kDecodeMin - 1) / kDecodeMin, (size_t)p0.n_chunks});
+  }
+  const int chunk = (int)saki::round_up((n + want - 1) / want, kTile);
+  const int n_chunks = (int)((n + chunk - 1) / chunk);
+  uint64_t* part = n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p0.part_off) : nullptr;
+  const long long groups = (long long)row_groups * n_chunks * n_bi;
+  hipLaunchKernelGGL((score_decode_kernel<RK, ST, R>), dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)),
+                     dim3(threads), 0, s, index, nt, N_valid, Q, q_pos, q, Bq, mu, H_q, H_kv,
+                     gq, n_bi, row_groups, chunk, n_chunks, k, top_idx, top_score, part);
+  if (n_chunks > 1)
+    hipLaunchKernelGGL((merge_kernel<KeysF32, false>), dim3((unsigned)rows),
+                       dim3(kWave * min(kMergeWaves, n_chunks)), 0, s, part, rows, n_chunks, k, top_idx,
+                       top_score, nullptr, nullptr);
+}
+
 template <int RK, int ST>
 void launch_score(const uint8_t* index, int B, int H_q, int H_kv, int index_heads, int N_cap,
                   int N_valid, const float* q, const int* q_pos, int Q, const float* Bq,
@@ -4340,34 +4528,28 @@ void launch_score(const uint8_t* index, int B, int H_q, int H_kv, int index_head
                        redo);
     return;
   }
-  const int cpg = p0.split ? p0.waves : 1;  // chunks per work-group
-  if (!p.mfma)
-    p = p.rows == 4 ? one_round(p0, score_stream_kernel<RK, ST, 4>, p0.row_blocks * B * index_heads, cpg, N_valid)
-                    : one_round(p0, score_stream_kernel<RK, ST, 1>, p0.row_blocks * B * index_heads, cpg, N_valid);
   const size_t rows = (size_t)B * H_q * Q;
-  uint64_t* part = p.n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p.part_off) : nullptr;
-  dim3 grid((unsigned)(p.row_blocks * ((p.n_chunks + cpg - 1) / cpg)), B * index_heads);
-  dim3 block(kWave * p.waves);
   const int nt = (int)saki::n_tiles(N_cap);
-  if (p.mfma) {
-    uint8_t* zq = ws + p.z_off;
-    float* zb = reinterpret_cast<float*>(ws + p.b_off);
-    const int parts = (Q + kQsRows - 1) / kQsRows;
-    const long long qs_groups = (long long)parts * B * H_q;
-    hipLaunchKernelGGL((query_sketch_kernel<RK, ST>), dim3((unsigned)(((qs_groups + kXcds - 1) / kXcds) * kXcds)),
-                       dim3(kQsWaves * kWave), 0, s, q, Bq, mu, Q, H_q, H_kv, B * H_q, parts, zq, zb);
-    hipLaunchKernelGGL((score_batch_kernel<RK, ST>), xcd_grid(p, B * H_q), dim3(kBWaves * kWave), 0,
-                       s, index, nt, N_valid, Q, q_pos, zq, zb, H_q, gq, B * H_q,
-                       p.row_blocks, p.chunk, p.n_chunks, k, top_idx, top_score, part);
+  if (!p.mfma) {
+    const int n_rho = gq * Q;
+    if (n_rho == 1)
+      launch_decode<RK, ST, 1>(index, nt, B, H_q, H_kv, gq, N_valid, q, q_pos, Q, Bq, mu, k, top_idx, top_score, ws, p0, s);
+    else if (n_rho == 2)
+      launch_decode<RK, ST, 2>(index, nt, B, H_q, H_kv, gq, N_valid, q, q_pos, Q, Bq, mu, k, top_idx, top_score, ws, p0, s);
+    else
+      launch_decode<RK, ST, 4>(index, nt, B, H_q, H_kv, gq, N_valid, q, q_pos, Q, Bq, mu, k, top_idx, top_score, ws, p0, s);
+    return;
   }
-  else if (p.rows == 4)
-    hipLaunchKernelGGL((score_stream_kernel<RK, ST, 4>), grid, block, 0, s, index, nt, N_valid,
-                       Q, q_pos, q, Bq, mu, H_q, H_kv, gq, p.row_blocks, p.chunk, p.n_chunks,
-                       (int)p.split, k, top_idx, top_score, part);
-  else
-    hipLaunchKernelGGL((score_stream_kernel<RK, ST, 1>), grid, block, 0, s, index, nt, N_valid,
-                       Q, q_pos, q, Bq, mu, H_q, H_kv, gq, p.row_blocks, p.chunk, p.n_chunks,
-                       (int)p.split, k, top_idx, top_score, part);
+  uint64_t* part = p.n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p.part_off) : nullptr;
+  uint8_t* zq = ws + p.z_off;
+  float* zb = reinterpret_cast<float*>(ws + p.b_off);
+  const int parts = (Q + kQsRows - 1) / kQsRows;
+  const long long qs_groups = (long long)parts * B * H_q;
+  hipLaunchKernelGGL((query_sketch_kernel<RK, ST>), dim3((unsigned)(((qs_groups + kXcds - 1) / kXcds) * kXcds)),
+                     dim3(kQsWaves * kWave), 0, s, q, Bq, mu, Q, H_q, H_kv, B * H_q, parts, zq, zb);
+  hipLaunchKernelGGL((score_batch_kernel<RK, ST>), xcd_grid(p, B * H_q), dim3(kBWaves * kWave), 0,
+                     s, index, nt, N_valid, Q, q_pos, zq, zb, H_q, gq, B * H_q,
+                     p.row_blocks, p.chunk, p.n_chunks, k, top_idx, top_score, part);
   if (p.n_chunks > 1)
     hipLaunchKernelGGL((merge_kernel<KeysF32, false>), dim3((unsigned)rows),
                        dim3(kWave * min(kMergeWaves, p.n_chunks)), 0, s, part, rows, p.n_chunks,

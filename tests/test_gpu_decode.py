@@ -1,0 +1,103 @@
+"""The decode scorer (Q < 16): head gate, tail candidates, their cuts and the
+online selection, against a stable sort of float64 scores of the exported codes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+S = pytest.importorskip("paper_2608_03228_amd.saki")
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+D = 128
+
+
+def _run(keys, q, r, sketch, k=64, shared=False, q_pos=None, seed=0):
+    """Index and lists of random factors; exported codes as float64."""
+    B, H_kv, N, _ = keys.shape
+    H_q = q.shape[1]
+    sets = H_kv if shared else H_q
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    B_k = torch.randn((sets, D, r), generator=g, device=DEV) / D ** 0.5
+    B_q = torch.randn((H_q, D, r), generator=g, device=DEV) / D ** 0.5
+    mu = torch.zeros((H_kv, D), device=DEV)
+    index = S.saki_build_index(keys, B_k, mu, r, sketch, sets)
+    idx, sc = S.saki_score_topk(index, sketch, q, B_q, mu, H_kv, N, N, r, q_pos=q_pos, k=k,
+                                index_heads=sets)
+    codes = S.saki_index_export(index, sketch, B, sets, N, r).double()
+    return idx.cpu().numpy(), sc.cpu().numpy(), codes, B_q
+
+
+def _check(keys, q, r, sketch, k=64, shared=False, q_pos=None):
+    """Scores within float32 sums (r + 128 products, 2^-24 each, of the absolute
+    sums) and a bf16 rounding of z next to a midpoint (2^-8) of float64 ones,
+    in order, and no key left out that beats the last one by more."""
+    B, H_kv, N, _ = keys.shape
+    H_q, Q = q.shape[1:3]
+    idx, sc, codes, B_q = _run(keys, q, r, sketch, k, shared, q_pos)
+    for b in range(B):
+        for h in range(H_q):
+            c = codes[b, (h // (H_q // H_kv)) if shared else h]
+            z = q[b, h].double() @ B_q[h].double()
+            if sketch != "f32":
+                z = z.to(torch.float32).to(torch.bfloat16).double()
+            s = (z @ c.T).cpu().numpy()
+            tol = ((z.abs() @ c.abs().T).cpu().numpy()) * 1e-5 + 1e-30
+            if sketch != "f32":  # an element of z next to a bf16 midpoint
+                tol += 2.0 ** -8 * float(z.abs().max()) * c.abs().max(dim=1).values.cpu().numpy()
+            for i in range(Q):
+                lim = N if q_pos is None else min(N, int(q_pos[i]) + 1)
+                n = max(0, min(k, lim))
+                got, val = idx[b, h, i], sc[b, h, i]
+                assert np.all(got[n:] == -1) and np.all(val[n:] == -np.inf)
+                got, val = got[:n], val[:n]
+                assert len(set(got.tolist())) == n and np.all((got >= 0) & (got < lim))
+                assert np.all(np.abs(val - s[i, got]) <= tol[i, got])
+                up = (val[1:] > val[:-1]) | ((val[1:] == val[:-1]) & (got[1:] < got[:-1]))
+                assert not up.any(), (b, h, i)
+                if n and n < lim:
+                    left = np.setdiff1d(np.arange(lim), got)
+                    assert np.all(s[i, left] <= val[-1] + tol[i, left] + tol[i, got[-1]]), (b, h, i)
+
+
+# one tile and its edges; the candidates' room (512 and 1,024 keys); the head
+# (4,096 and 8,192 keys) and its edges; chunks and rounds; every row group size
+@pytest.mark.parametrize("N,Q,H_q,H_kv,shared,r,sketch", [
+    (1, 1, 2, 1, False, 32, "bf16"), (63, 1, 2, 1, False, 16, "fp8"), (65, 3, 2, 2, False, 32, "f32"),
+    (512, 1, 4, 1, True, 32, "bf16"), (513, 2, 2, 1, False, 64, "fp8"), (1025, 1, 2, 1, False, 128, "bf16"),
+    (8191, 1, 7, 1, True, 32, "bf16"), (8193, 1, 1, 1, False, 32, "f32"), (8256, 5, 2, 1, True, 128, "f32"),
+    (16385, 2, 2, 1, False, 128, "fp8"), (40001, 15, 2, 1, True, 64, "f32"), (300007, 1, 4, 1, True, 16, "fp8"),
+    (700001, 1, 2, 1, False, 32, "bf16"), (100003, 4, 16, 4, True, 32, "fp8")])
+def test_decode_lists(N, Q, H_q, H_kv, shared, r, sketch):
+    g = torch.Generator(device=DEV).manual_seed(N)
+    keys = torch.randn((1, H_kv, N, D), generator=g, device=DEV)
+    q = torch.randn((1, H_q, Q, D), generator=g, device=DEV)
+    _check(keys, q, r, sketch, shared=shared)
+
+
+def test_decode_causal_and_short_k():
+    """Rows with no key, fewer than k, limits on tile and head edges."""
+    g = torch.Generator(device=DEV).manual_seed(1)
+    keys = torch.randn((2, 1, 9000, D), generator=g, device=DEV)
+    pos = torch.tensor([-1, 0, 62, 63, 64, 4095, 8191, 8192, 20000], dtype=torch.int32, device=DEV)
+    q = torch.randn((2, 2, len(pos), D), generator=g, device=DEV)
+    _check(keys, q, 32, "bf16", k=10, q_pos=pos)
+    _check(keys, q, 32, "f32", q_pos=pos, shared=True)
+
+
+@pytest.mark.parametrize("order", ["equal", "rising", "falling"])
+def test_decode_candidates_that_overflow(order):
+    """Many equal scores, and scores that rise along the keys (every tail key
+    beats the gate): the online selection."""
+    N = 60_000
+    g = torch.Generator(device=DEV).manual_seed(2)
+    base = torch.randn(D, generator=g, device=DEV)
+    scale = {"equal": torch.ones(N, device=DEV), "rising": torch.linspace(-1, 1, N, device=DEV),
+             "falling": torch.linspace(1, -1, N, device=DEV)}[order]
+    keys = (scale[:, None] * base)[None, None].contiguous()
+    q = base.expand(1, 4, 1, D).contiguous()
+    if order == "equal":
+        idx, sc, _, _ = _run(keys, q, 32, "bf16", shared=True)
+        assert np.array_equal(idx, np.broadcast_to(np.arange(64), idx.shape))
+        assert np.all(sc == sc[..., :1])
+    else:
+        _check(keys, q, 32, "f32", shared=True)
