@@ -990,8 +990,11 @@ struct MfmaScorer {
     uint4 v[4][NL];
   };
   // the next tile is loaded while the current one is scored when its raw
-  // operands fit in 32 registers
+  // operands fit in 32 registers (in for_tiles_deep 64, see there)
   static constexpr bool kPrefetch = 4 * NL <= 8;
+  static constexpr bool kPrefetchWide = 4 * NL <= 16;
+  // scores good to a bf16 rounding of both operands from the bf16 MFMA
+  static constexpr bool kApprox = !SBF && RK >= 32;
 
   __device__ __forceinline__ void load(const uint8_t* tb, int qi, int g, Raw& r) const {
 #pragma unroll
@@ -1060,6 +1063,33 @@ struct MfmaScorer {
     }
   }
 
+  // The same for float32 codes with both operands rounded to bf16: a step of
+  // the bf16 MFMA takes dims 32 kk + 4 g .. + 3 and 32 kk + 16 + 4 g .. + 3 of
+  // lane group g, two of the raw pieces, in a 16th of the float32 MFMA's time.
+  __device__ __forceinline__ void mma_approx(const Raw& r, f32x4_t acc[4]) const {
+    if constexpr (kApprox) {
+      bf16x8_t z[RK / 32];
+#pragma unroll
+      for (int kk = 0; kk < RK / 32; ++kk)
+        z[kk] = as_bf16x8(uint4{bf16x2_bits(zf[8 * kk], zf[8 * kk + 1]), bf16x2_bits(zf[8 * kk + 2], zf[8 * kk + 3]),
+                                bf16x2_bits(zf[8 * kk + 4], zf[8 * kk + 5]), bf16x2_bits(zf[8 * kk + 6], zf[8 * kk + 7])});
+#pragma unroll
+      for (int sub = 0; sub < 4; ++sub) {
+        f32x4_t a = {init, init, init, init};
+#pragma unroll
+        for (int kk = 0; kk < RK / 32; ++kk) {
+          const uint4 x = r.v[sub][2 * kk], y = r.v[sub][2 * kk + 1];
+          auto two = [](uint32_t lo, uint32_t hi) { return bf16x2_bits(__uint_as_float(lo), __uint_as_float(hi)); };
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              as_bf16x8(uint4{two(x.x, x.y), two(x.z, x.w), two(y.x, y.y), two(y.z, y.w)}), z[kk], a, 0, 0, 0);
+        }
+        acc[sub] = a;
+      }
+    } else {
+      mma(r, acc);
+    }
+  }
+
   // body(t0, acc) for the tiles t0 = t_beg, t_beg + step, ... < t_end
   template <class F>
   __device__ __forceinline__ void for_tiles(const uint8_t* hbase, int t_beg, int t_end, int step,
@@ -1095,31 +1125,45 @@ struct MfmaScorer {
 
   // body(t0, acc) for every tile of [t_beg, t_end) in order, with the loads
   // of the next DEPTH - 1 tiles in flight while one is scored (a ring of
-  // DEPTH register buffers) when a tile's operands fit in 32 registers;
-  // otherwise as for_tiles.  Loads past the last tile are clamped to it.
-  template <int DEPTH = 3, class F>
+  // DEPTH register buffers) when a tile's operands fit in 32 registers, of the
+  // next one when they fit in 64; otherwise as for_tiles.  Loads past the last
+  // tile are clamped to it.  APPROX: scores of mma_approx.
+  template <int DEPTH = 3, bool APPROX = false, class F>
   __device__ __forceinline__ void for_tiles_deep(const uint8_t* hbase, int t_beg, int t_end,
                                                  int qi, int g, F&& body) const {
-    if constexpr (kPrefetch) {
-      if (t_beg >= t_end) return;
+    auto form = [&](const Raw& r, f32x4_t* acc) {
+      if constexpr (APPROX)
+        mma_approx(r, acc);
+      else
+        mma(r, acc);
+    };
+    if (t_beg >= t_end) return;
+    if constexpr (kPrefetchWide) {
+      constexpr int N = kPrefetch ? DEPTH : 2;
       const int last = t_beg + ((t_end - 1 - t_beg) / kTile) * kTile;
       auto at = [&](int t) { return hbase + (size_t)(min(t, last) / kTile) * TB; };
-      Raw r[DEPTH];
+      Raw r[N];
 #pragma unroll
-      for (int d = 0; d + 1 < DEPTH; ++d) load(at(t_beg + d * kTile), qi, g, r[d]);
-      for (int t0 = t_beg;; t0 += DEPTH * kTile) {
+      for (int d = 0; d + 1 < N; ++d) load(at(t_beg + d * kTile), qi, g, r[d]);
+      for (int t0 = t_beg;; t0 += N * kTile) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
+        for (int d = 0; d < N; ++d) {
           const int t = t0 + d * kTile;
-          load(at(t + (DEPTH - 1) * kTile), qi, g, r[(d + DEPTH - 1) % DEPTH]);
+          load(at(t + (N - 1) * kTile), qi, g, r[(d + N - 1) % N]);
           f32x4_t acc[4];
-          mma(r[d], acc);
+          form(r[d], acc);
           body(t, acc);
           if (t + kTile >= t_end) return;
         }
       }
     } else {
-      for_tiles(hbase, t_beg, t_end, kTile, qi, g, body);
+      for (int t0 = t_beg; t0 < t_end; t0 += kTile) {
+        Raw cur;
+        load(hbase + (size_t)(t0 / kTile) * TB, qi, g, cur);
+        f32x4_t acc[4];
+        form(cur, acc);
+        body(t0, acc);
+      }
     }
   }
 };
@@ -1187,14 +1231,17 @@ __device__ __forceinline__ float mfma_query_sketch(const float* __restrict__ qr,
 // q[qi][16j + 4g .. 16j + 4g + 3] for j = 0..7 as float4 (each row read as
 // 64-byte runs) and feeds dims c = 16j + 4g + e at step 4j + e.  B_q of the
 // head waits in LDS in that operand order, one float4 per (j, mb) and lane.
-// grid: 1-D, work-group (bh, part) covers rows [part * kQsRows, ...) of (b, h).
+// grid: 1-D, work-group (bh, part) covers rows [part * rows_per, ...) of (b, h).
+// Few long heads are cut into shorter parts so that every CU has some: the
+// 32 x 4,032 rows of a layer take 10 us in 512 parts, 32 us in 128 of 1,024 rows.
 constexpr int kQsWaves = 4;
-constexpr int kQsRows = 1024;
+constexpr int kQsRows = 1024;   // rows per work-group, at most
+constexpr int kQsGroups = 512;  // work-groups wanted before a work-group takes more than 64 rows
 
 template <int RK, int ST>
 __global__ __launch_bounds__(kQsWaves * kWave) void query_sketch_kernel(
     const float* __restrict__ q, const float* __restrict__ Bq, const float* __restrict__ mu,
-    int Q, int H_q, int H_kv, int n_bh, int parts, uint8_t* __restrict__ zq,
+    int Q, int H_q, int H_kv, int n_bh, int parts, int rows_per, uint8_t* __restrict__ zq,
     float* __restrict__ bout) {
   constexpr int D = saki::kHeadDim;
   constexpr int MB = RK / 16;
@@ -1219,8 +1266,8 @@ __global__ __launch_bounds__(kQsWaves * kWave) void query_sketch_kernel(
   float4 mv[8];  // this lane's dims of mu
 #pragma unroll
   for (int j = 0; j < 8; ++j) mv[j] = *reinterpret_cast<const float4*>(mr + 16 * j + 4 * g);
-  const int r_end = min(Q, (part + 1) * kQsRows);
-  for (int row0 = part * kQsRows + wave * kMR; row0 < r_end; row0 += kQsWaves * kMR) {
+  const int r_end = min(Q, (part + 1) * rows_per);
+  for (int row0 = part * rows_per + wave * kMR; row0 < r_end; row0 += kQsWaves * kMR) {
     const int row = row0 + qi;
     const bool ok = row < r_end;
     const float* qr = q + (bh * Q + (ok ? row : row0)) * D;
@@ -1293,6 +1340,10 @@ __global__ __launch_bounds__(kQsWaves * kWave) void query_sketch_kernel(
 //   B. every key that scores >= tau goes to its lane's candidate slots (39
 //      per lane usable, 156 per row), and the row's count is checked to be
 //      >= 64.
+// With that check any tau is safe, so pass A may take rounded scores: float32
+// codes of 32 and more dims go through the bf16 MFMA there (the float32 one
+// bounds this kernel for them: at r = 64, 64 instructions of 32 clocks a tile
+// against 8 of 16).
 // The candidates are then sorted by a bitonic network that holds 16 entries
 // per lane, and the best 64 are kept.  A row whose candidates overflow its
 // slots (many equal scores, or rows of very different lengths in one wave)
@@ -1556,7 +1607,7 @@ __global__ __launch_bounds__(kBWaves * kWave) void score_batch_kernel(
     bmax = vmax(bmax, x);
     bmin = ok ? vmin(bmin, x) : bmin;
   };
-  sc.template for_tiles_deep<kBDepth>(hbase, kbeg, kend, qi, g, [&](int t0, f32x4_t* acc) {
+  sc.template for_tiles_deep<kBDepth, Scorer::kApprox>(hbase, kbeg, kend, qi, g, [&](int t0, f32x4_t* acc) {
     const int tl = (t0 - kbeg) / kTile;
     const int wo = (tl * 4 * lane_ent + g * lane_ent) / 2;  // this lane's first word
     if (t0 + kTile <= kmin && lane_ent <= 4) {
@@ -4543,10 +4594,12 @@ void launch_score(const uint8_t* index, int B, int H_q, int H_kv, int index_head
   uint64_t* part = p.n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p.part_off) : nullptr;
   uint8_t* zq = ws + p.z_off;
   float* zb = reinterpret_cast<float*>(ws + p.b_off);
-  const int parts = (Q + kQsRows - 1) / kQsRows;
+  int rows_per = kQsRows;
+  while (rows_per > kQsWaves * kMR && (long long)((Q + rows_per - 1) / rows_per) * B * H_q < kQsGroups) rows_per /= 2;
+  const int parts = (Q + rows_per - 1) / rows_per;
   const long long qs_groups = (long long)parts * B * H_q;
   hipLaunchKernelGGL((query_sketch_kernel<RK, ST>), dim3((unsigned)(((qs_groups + kXcds - 1) / kXcds) * kXcds)),
-                     dim3(kQsWaves * kWave), 0, s, q, Bq, mu, Q, H_q, H_kv, B * H_q, parts, zq, zb);
+                     dim3(kQsWaves * kWave), 0, s, q, Bq, mu, Q, H_q, H_kv, B * H_q, parts, rows_per, zq, zb);
   hipLaunchKernelGGL((score_batch_kernel<RK, ST>), xcd_grid(p, B * H_q), dim3(kBWaves * kWave), 0,
                      s, index, nt, N_valid, Q, q_pos, zq, zb, H_q, gq, B * H_q,
                      p.row_blocks, p.chunk, p.n_chunks, k, top_idx, top_score, part);
