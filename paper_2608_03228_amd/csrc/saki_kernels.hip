@@ -2,6 +2,7 @@
 //
 // Kernels (all on the caller's stream):
 //   build_index_kernel   key codes c = B_k^T (k - mu) for every query head (Eq. 4)
+//   append_index_kernel  the same for a few keys
 //   score_batch_kernel   z = B_q^T q, b = q^T mu and s = z . c + b on MFMA for
 //                        blocks of 16 query rows, top-64 per row (two passes:
 //                        block maxima and a threshold, then the candidates)
@@ -453,6 +454,84 @@ __global__ __launch_bounds__(kBuildWaves * kWave) void build_index_kernel(
       }
     }
   }
+}
+
+// Codes of a few appended keys (a decode step's newest one): one wave per 16
+// code dimensions of a code set, the same products in the same order as
+// build_index_kernel (so an index grown key by key equals one built at once),
+// with B_k split in the registers that its loads fill.  Latency bounds it: one
+// round of loads, 24 MFMAs, no LDS and no barrier.  One key of 32 heads took
+// 6.8 us in build_index_kernel, which stages the terms of B_k in LDS for many
+// keys; past one MFMA tile of keys it is the better one.
+constexpr int kAppendKeys = 16;
+template <int RK, bool KBF, int ST>
+__global__ __launch_bounds__(kWave) void append_index_kernel(
+    const void* __restrict__ keys, const float* __restrict__ Bk, const float* __restrict__ mu, int H_q,
+    int H_kv, int N_cap, int n_tiles, uint8_t* __restrict__ index, int n_begin, int n_count) {
+  constexpr int D = saki::kHeadDim;
+  constexpr int ES = code_bytes<ST>();
+  const int mc = blockIdx.x, h = blockIdx.y;
+  const size_t b = blockIdx.z;
+  const int gkv = h / (H_q / H_kv);
+  const int lane = lane_id(), qi = lane % 16, g = lane / 16;
+  const bool ok = qi < n_count;
+  const int n = n_begin + (ok ? qi : 0);
+  // lane (qi, g): dims 32 kk + 8 g + e of B_k's column 16 mc + qi and of key qi
+  const float* wp = Bk + ((size_t)h * D + 8 * g) * RK + 16 * mc + qi;
+  float w[4][8], x[4][8];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[kk][e] = wp[(size_t)(32 * kk + e) * RK];
+  const size_t kr = ((b * H_kv + gkv) * N_cap + n) * D + 8 * g;
+  const float* mr = mu + (size_t)gkv * D + 8 * g;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) {
+      const float4 kv = load_key4<KBF>(keys, kr + 32 * kk + e);
+      const float4 mv = *reinterpret_cast<const float4*>(mr + 32 * kk + e);
+      x[kk][e] = ok ? kv.x - mv.x : 0.f;
+      x[kk][e + 1] = ok ? kv.y - mv.y : 0.f;
+      x[kk][e + 2] = ok ? kv.z - mv.z : 0.f;
+      x[kk][e + 3] = ok ? kv.w - mv.w : 0.f;
+    }
+  f32x4_t hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    uint32_t wt[4][3], xt[4][3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      split3_bf16x2(w[kk][2 * e], w[kk][2 * e + 1], wt[e]);
+      split3_bf16x2(x[kk][2 * e], x[kk][2 * e + 1], xt[e]);
+    }
+    bf16x8_t wv[3], xv[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      wv[p] = as_bf16x8(uint4{wt[0][p], wt[1][p], wt[2][p], wt[3][p]});
+      xv[p] = as_bf16x8(uint4{xt[0][p], xt[1][p], xt[2][p], xt[3][p]});
+    }
+    hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[0], xv[0], hi, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[2], xv[0], lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[1], xv[1], lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[0], xv[2], lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[1], xv[0], lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[0], xv[1], lo, 0, 0, 0);
+  }
+  hi += lo;
+  if (!ok) return;
+  const int m = 16 * mc + 4 * g;  // first code dim of this lane
+  uint8_t* dst = index + ((b * H_q + h) * n_tiles + n / kTile) * ((size_t)kTile * RK * ES) +
+                 (size_t)(m * ES / 16) * kTile * 16 + (size_t)(n % kTile) * 16 + (m * ES) % 16;
+  if constexpr (ST == kStFp8)
+    *reinterpret_cast<uint32_t*>(dst) =
+        e4m3_bits(hi[0]) | (e4m3_bits(hi[1]) << 8) | (e4m3_bits(hi[2]) << 16) | (e4m3_bits(hi[3]) << 24);
+  else if constexpr (ST == kStBf16)
+    *reinterpret_cast<uint2*>(dst) =
+        uint2{bf16_bits(hi[0]) | (bf16_bits(hi[1]) << 16), bf16_bits(hi[2]) | (bf16_bits(hi[3]) << 16)};
+  else
+    *reinterpret_cast<uint4*>(dst) = uint4{__float_as_uint(hi[0]), __float_as_uint(hi[1]), __float_as_uint(hi[2]),
+                                           __float_as_uint(hi[3])};
 }
 
 // grid (tiles, B*H_q), block 64: codes -> float [B, H_q, N_cap, r].
@@ -4451,6 +4530,11 @@ template <int RK, bool KBF, int ST>
 void launch_build(const void* keys, const float* Bk, const float* mu, int B, int H_q,
                   int H_kv, int N_cap, uint8_t* index, int n_begin, int n_end,
                   hipStream_t s) {
+  if (n_end - n_begin <= kAppendKeys) {
+    hipLaunchKernelGGL((append_index_kernel<RK, KBF, ST>), dim3(RK / 16, H_q, B), dim3(kWave), 0, s, keys, Bk, mu, H_q,
+                       H_kv, N_cap, (int)saki::n_tiles(N_cap), index, n_begin, n_end - n_begin);
+    return;
+  }
   const int k0 = (n_begin / 16) * 16;
   const int per_head = n_end - n_begin <= kBuildSplitKeys ? 1 : 0;
   const long long units = (long long)(per_head ? H_q : H_kv) * B;
