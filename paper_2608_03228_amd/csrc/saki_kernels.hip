@@ -4069,28 +4069,58 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return v;
 }
 
-// sin and cos of pos * inv (radians): the product and its reduction to
-// [-pi, pi] in float64, the functions in float32.
-__device__ __forceinline__ void rope_sincos(int pos, double inv, float* s, float* c) {
-  constexpr double kTwoPi = 6.283185307179586476925286766559;
-  const double a = (double)pos * inv;
-  const float red = (float)(a - kTwoPi * rint(a / kTwoPi));
-  sincosf(red, s, c);
+// theta^(-2l/d) in quarter turns per position.
+__device__ __forceinline__ double rope_quarter_turns(int l, float log_theta) {
+  constexpr double kTwoOverPi = 0.63661977236758134307553505349006;
+  return exp(-(2.0 * l / saki::kHeadDim) * (double)log_theta) * kTwoOverPi;
+}
+// Sine and cosine of a quarter turns, a in float64: the nearest whole number n
+// of them is taken off exactly, the rest (at most pi / 4) goes through the
+// Taylor series (T: float to x^9 / x^10, double to x^13 / x^14, each below
+// half a float32 step), and n picks the quadrant.
+template <class T>
+__device__ __forceinline__ void rope_sincos_quarters(double a, float* s, float* c) {
+  constexpr double kHalfPi = 1.57079632679489661923132169163975;
+  const double n = rint(a);
+  const T x = (T)((a - n) * kHalfPi), y = x * x;
+  T sp = (T)0, cp = (T)0;
+  if constexpr (sizeof(T) == 8) {
+    sp = fma(y, (T)(1.0 / 6227020800.0), (T)(-1.0 / 39916800.0));
+    sp = fma(y, sp, (T)(1.0 / 362880.0));
+    cp = fma(y, (T)(-1.0 / 87178291200.0), (T)(1.0 / 479001600.0));
+    cp = fma(y, cp, (T)(-1.0 / 3628800.0));
+  } else {
+    sp = (T)(1.0 / 362880.0);
+    cp = (T)(-1.0 / 3628800.0);
+  }
+  sp = fma(y, sp, (T)(-1.0 / 5040.0));
+  sp = fma(y, sp, (T)(1.0 / 120.0));
+  sp = fma(y, sp, (T)(-1.0 / 6.0));
+  sp = fma(y * x, sp, x);
+  cp = fma(y, cp, (T)(1.0 / 40320.0));
+  cp = fma(y, cp, (T)(-1.0 / 720.0));
+  cp = fma(y, cp, (T)(1.0 / 24.0));
+  cp = fma(y, cp, (T)(-0.5));
+  cp = fma(y, cp, (T)1.0);
+  const int m = (int)(n - 4.0 * floor(0.25 * n));  // n mod 4
+  const float sv = (float)((m & 1) ? cp : sp), cv = (float)((m & 1) ? sp : cp);
+  *s = (m & 2) ? -sv : sv;
+  *c = ((m + 1) & 2) ? -cv : cv;
 }
 
-constexpr int kAttendWaves = 4;   // waves per row
-constexpr int kAttendBatch = 16;  // list entries per wave: wave w takes 16w .. 16w + 15
-
-// grid (Q, B * H_q), block 256: one work-group per (sequence, head, query)
-// row, k <= 64.  Lane l holds dims l and l + 64 of the rotated query and of
-// each key, so that the RoPE pairs (m, m + d/2) stay inside a lane, and a
-// key's score is a wave sum.  Each wave gathers its 16 entries' keys (or, for
-// reconstruction, unpacks their codes into LDS and forms mu + B_q c) and
-// values in one round of loads, and keeps the softmax of its entries relative
-// to its own maximum; the four partial results are then rescaled to the
-// row's maximum and added.
-template <int RK, bool KBF, int ST, bool RECON>
-__global__ __launch_bounds__(kAttendWaves * kWave) void attend_kernel(
+// grid (Q, B * H_q), block 64 W: one work-group per (sequence, head, query)
+// row, k <= 64.  Lane l holds dims l and l + 64 of the query and of each key, so
+// that the RoPE pairs (m, m + d/2) stay inside a lane, and a key's score is a
+// wave sum of the pairs' products turned by the position difference:
+// rope(q, pos) . rope(k, j) depends on pos - j only.  Each wave gathers its
+// 64 / W entries' keys (or, for reconstruction, unpacks their codes into LDS
+// and forms mu + B_q c) and values in one round of loads, and keeps the softmax
+// of its entries relative to its own maximum; the W partial results are then
+// rescaled to the row's maximum and added.  Few rows are bound by the chain of
+// one wave (W = 16 up to kAttendFewRows rows), many by the work in all (W = 4).
+constexpr int kAttendFewRows = 512;
+template <int RK, bool KBF, int ST, bool RECON, int W>
+__global__ __launch_bounds__(W * kWave) void attend_kernel(
     const void* __restrict__ keys, const float* __restrict__ values,
     const uint8_t* __restrict__ index, int n_tiles, int H_q, int H_kv, int index_heads,
     int N_cap, int N_valid, const float* __restrict__ q, const int* __restrict__ q_pos, int Q,
@@ -4099,7 +4129,7 @@ __global__ __launch_bounds__(kAttendWaves * kWave) void attend_kernel(
   constexpr int D = saki::kHeadDim;
   constexpr int HALF = D / 2;
   static_assert(HALF == kWave, "one RoPE pair per lane");
-  static_assert(kAttendWaves * kAttendBatch == kWave, "the waves cover a 64-entry list");
+  constexpr int kAttendWaves = W, kAttendBatch = kWave / W;  // list entries per wave: wave w's are consecutive
   constexpr int ES = code_bytes<ST>();
   constexpr int CPP = saki::kChunkBytes / ES;
   constexpr int NP = RK / CPP;
@@ -4118,21 +4148,15 @@ __global__ __launch_bounds__(kAttendWaves * kWave) void attend_kernel(
   const size_t kbase = ((size_t)b * H_kv + g) * N_cap;
   const size_t cset = b * index_heads + h / (H_q / index_heads);
   const int e0 = wave * kAttendBatch;
-  // lane u < 16: list entry e0 + u (-1 past k)
+  // lane u < kAttendBatch: list entry e0 + u (-1 past k)
   const int my_j = lane < kAttendBatch && e0 + lane < k ? top_idx[row * k + e0 + lane] : -1;
   if constexpr (RECON) {
     for (int e = threadIdx.x; e < D * RK; e += blockDim.x)
       bq_s[e / RK][e % RK] = Bq[(size_t)h * D * RK + e];
   }
-  const double inv = exp(-(2.0 * lane / D) * (double)log_theta);  // theta^(-2l/d)
-  float qa, qb;
-  {
-    float sn, cs;
-    rope_sincos(q_pos ? q_pos[i] : N_valid - 1, inv, &sn, &cs);
-    const float a0 = q[row * D + lane], a1 = q[row * D + lane + HALF];
-    qa = a0 * cs - a1 * sn;
-    qb = a1 * cs + a0 * sn;
-  }
+  const double turn = rope_quarter_turns(lane, log_theta);
+  const int pos = q_pos ? q_pos[i] : N_valid - 1;
+  const float qa = q[row * D + lane], qb = q[row * D + lane + HALF];
   int jj[kAttendBatch];
 #pragma unroll
   for (int u = 0; u < kAttendBatch; ++u) {
@@ -4191,9 +4215,9 @@ __global__ __launch_bounds__(kAttendWaves * kWave) void attend_kernel(
 #pragma unroll
   for (int u = 0; u < kAttendBatch; ++u) {
     float sn, cs;
-    rope_sincos(max(jj[u], 0), inv, &sn, &cs);
-    const float kb0 = k0[u] * cs - k1[u] * sn, kb1 = k1[u] * cs + k0[u] * sn;
-    const float sc = wave_sum_f32(fmaf(qa, kb0, qb * kb1)) * (1.f / 11.313708498984761f);
+    rope_sincos_quarters<float>(((double)pos - (double)max(jj[u], 0)) * turn, &sn, &cs);
+    const float re = fmaf(qa, k0[u], qb * k1[u]), im = fmaf(qb, k0[u], -(qa * k1[u]));
+    const float sc = wave_sum_f32(fmaf(cs, re, -(sn * im))) * (1.f / 11.313708498984761f);
     if (lane == u && jj[u] >= 0) my_s = sc;
   }
   // this wave's softmax terms relative to its own maximum
@@ -4253,45 +4277,6 @@ constexpr int kRotLo = 64;
 constexpr int kRotRows = 256;          // 128 KiB of LDS
 constexpr int kAttendManyRows = 4096;
 constexpr int kAttendRowsMaxCap = 1 << 22;  // a head's keys within 32-bit byte offsets
-
-// theta^(-2l/d) in quarter turns per position.
-__device__ __forceinline__ double rope_quarter_turns(int l, float log_theta) {
-  constexpr double kTwoOverPi = 0.63661977236758134307553505349006;
-  return exp(-(2.0 * l / saki::kHeadDim) * (double)log_theta) * kTwoOverPi;
-}
-// Sine and cosine of a quarter turns, a in float64: the nearest whole number n
-// of them is taken off exactly, the rest (at most pi / 4) goes through the
-// Taylor series (T: float to x^9 / x^10, double to x^13 / x^14, each below
-// half a float32 step), and n picks the quadrant.
-template <class T>
-__device__ __forceinline__ void rope_sincos_quarters(double a, float* s, float* c) {
-  constexpr double kHalfPi = 1.57079632679489661923132169163975;
-  const double n = rint(a);
-  const T x = (T)((a - n) * kHalfPi), y = x * x;
-  T sp = (T)0, cp = (T)0;
-  if constexpr (sizeof(T) == 8) {
-    sp = fma(y, (T)(1.0 / 6227020800.0), (T)(-1.0 / 39916800.0));
-    sp = fma(y, sp, (T)(1.0 / 362880.0));
-    cp = fma(y, (T)(-1.0 / 87178291200.0), (T)(1.0 / 479001600.0));
-    cp = fma(y, cp, (T)(-1.0 / 3628800.0));
-  } else {
-    sp = (T)(1.0 / 362880.0);
-    cp = (T)(-1.0 / 3628800.0);
-  }
-  sp = fma(y, sp, (T)(-1.0 / 5040.0));
-  sp = fma(y, sp, (T)(1.0 / 120.0));
-  sp = fma(y, sp, (T)(-1.0 / 6.0));
-  sp = fma(y * x, sp, x);
-  cp = fma(y, cp, (T)(1.0 / 40320.0));
-  cp = fma(y, cp, (T)(-1.0 / 720.0));
-  cp = fma(y, cp, (T)(1.0 / 24.0));
-  cp = fma(y, cp, (T)(-0.5));
-  cp = fma(y, cp, (T)1.0);
-  const int m = (int)(n - 4.0 * floor(0.25 * n));  // n mod 4
-  const float sv = (float)((m & 1) ? cp : sp), cv = (float)((m & 1) ? sp : cp);
-  *s = (m & 2) ? -sv : sv;
-  *c = ((m + 1) & 2) ? -cv : cv;
-}
 
 // v of lane N of this lane's row of 16
 template <int N>
@@ -4511,9 +4496,13 @@ void launch_attend(const void* keys, const float* values, const uint8_t* index, 
     }
   }
   dim3 grid((unsigned)Q, (unsigned)(B * H_q));
-  hipLaunchKernelGGL((attend_kernel<RK, KBF, ST, RECON>), grid, dim3(kAttendWaves * kWave), 0, s,
-                     keys, values, index, (int)saki::n_tiles(N_cap), H_q, H_kv, index_heads, N_cap,
-                     N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), out);
+  const int nt = (int)saki::n_tiles(N_cap);
+  if (rows <= (size_t)kAttendFewRows)
+    hipLaunchKernelGGL((attend_kernel<RK, KBF, ST, RECON, 16>), grid, dim3(16 * kWave), 0, s, keys, values, index, nt,
+                       H_q, H_kv, index_heads, N_cap, N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), out);
+  else
+    hipLaunchKernelGGL((attend_kernel<RK, KBF, ST, RECON, 4>), grid, dim3(4 * kWave), 0, s, keys, values, index, nt,
+                       H_q, H_kv, index_heads, N_cap, N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), out);
 }
 
 // ---------------------------------------------------------------- dispatch helpers
@@ -5063,7 +5052,6 @@ int saki_attend(const void* keys, int key_dtype, const float* values, const void
     if (!keys) return SAKI_ERR_ARG;
     if (!dtype_ok(key_dtype)) return SAKI_ERR_UNSUPPORTED;
   }
-  if ((Q + kAttendWaves - 1) / kAttendWaves > 0x7fffffff) return SAKI_ERR_UNSUPPORTED;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const uint8_t* ix = reinterpret_cast<const uint8_t*>(index);
 #define SAKI_ATTEND(RK, KB, ST, RC)                                                              \
