@@ -181,26 +181,49 @@ def saki_recall_workspace_bytes(B, H_q, H_kv, Q, N_valid, d, k) -> int:
 
 # ------------------------------------------------------------------ GPU calls
 
+_torch_mod = None
+_raw_stream = _get_device = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod, _raw_stream, _get_device
+    if _torch_mod is None:
+        import torch
+        # the current stream's handle without building a Stream object
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _get_device = getattr(torch._C, "_cuda_getDevice", None)
+        _torch_mod = torch
+    return _torch_mod
 
 
+# A decode step is three calls of 20-40 us of GPU work in all, so a call's
+# checks and marshalling count: no import, Stream object, size query or ctypes
+# object that the call does not need (33 us a step at 4,001 keys).
 def _dev(t, dtypes, name):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if isinstance(t, _torch().Tensor) and t.is_cuda and t.dtype in dtypes and t.is_contiguous():
+        return t.data_ptr()
+    if not isinstance(t, _torch().Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
+
+
+def _plain(*sizes):
+    """Whether the sizes are Python ints (others go to the size query, whose
+    argument types decide what is taken)."""
+    for v in sizes:
+        if type(v) is not int:
+            return False
+    return True
 
 
 def _stream(stream):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and _get_device is not None:
+        return _raw_stream(_get_device())
+    return _torch().cuda.current_stream().cuda_stream
 
 
 def _key_dtype(keys):
@@ -240,7 +263,8 @@ def saki_build_index(keys, B_k, mu, r: int, sketch: str, H_q: int, index=None,
     torch = _torch()
     kp = _dev(keys, (torch.float32, torch.bfloat16), "keys")
     B, H_kv, N_cap, d = keys.shape
-    nbytes = saki_index_bytes(B, H_q, N_cap, r, sketch)
+    if index is None or not _plain(H_q, r):
+        nbytes = saki_index_bytes(B, H_q, N_cap, r, sketch)
     if index is None:
         index = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=keys.device)
     n_count = N_cap - n_begin if n_count is None else n_count
@@ -273,7 +297,8 @@ def saki_score_topk(index, sketch: str, q, B_q, mu, H_kv: int, N_cap: int, N_val
     qp = _dev(q, (torch.float32,), "q")
     B, H_q, Q, d = q.shape
     ih = H_q if index_heads is None else int(index_heads)
-    need = saki_score_topk_workspace_bytes(B, H_q, Q, N_valid, r, k, sketch, ih)
+    if ws is None or not _plain(N_valid, r, k):
+        need = saki_score_topk_workspace_bytes(B, H_q, Q, N_valid, r, k, sketch, ih)
     if ws is None:
         ws = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
     if top_idx is None:
@@ -325,7 +350,8 @@ def saki_recall(keys, q, approx_idx, N_valid: int, q_pos=None, k: int = 64, ws=N
     qp = _dev(q, (torch.float32,), "q")
     B, H_kv, N_cap, d = keys.shape
     _, H_q, Q, _ = q.shape
-    need = saki_recall_workspace_bytes(B, H_q, H_kv, Q, N_valid, d, k)
+    if ws is None or not _plain(N_valid, k):
+        need = saki_recall_workspace_bytes(B, H_q, H_kv, Q, N_valid, d, k)
     if ws is None:
         ws = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
     if hits is None:
