@@ -4256,7 +4256,7 @@ __global__ __launch_bounds__(W * kWave) void attend_kernel(
   out[row * D + lane + HALF] = a1 * il;
 }
 
-// attend_rows_kernel: the same attention for many rows and exact keys.  A row
+// attend_rows_kernel: the same attention for many rows.  A row
 // costs one gather of its listed keys and values (64 KB, from L2) and, with a
 // wave sum and 64 sines and cosines per key, was bound by the VALU (about 90
 // operations per key and wave; 1,147 us for 129,024 rows over 4,096 keys).
@@ -4270,12 +4270,21 @@ __global__ __launch_bounds__(W * kWave) void attend_kernel(
 //     both in LDS (64 low and n_hi high rows, float32 values rounded from
 //     float64): an angle sum costs four operations.  A step with another
 //     difference evaluates its angles (reduced in float64).
+//   - Reconstructed keys are a contraction, mu + B_q c: the codes of 16 listed
+//     keys (rows) times the head's B_q (columns, in the order of the dims above,
+//     so that a lane receives just its own) on the bf16 MFMA.  B_q waits in LDS
+//     as three bf16 terms per element (see build_index_kernel), read once for
+//     32 keys; float32 codes are split too (six products, the small ones
+//     first).  As r FMAs a key and dim, 19,200 rows took 262 us at r = 32 and
+//     96,000 rows 10 ms at r = 128 with float32 codes.
 // The work-groups stay for the whole launch (one per CU, the table takes its
-// LDS), which pays from kAttendManyRows rows on.
+// LDS), which pays from kAttendManyRows rows on, and with B_q staged per head
+// from kAttendHeadRows rows of a head.
 constexpr int kAttendRowWaves = 16;
 constexpr int kRotLo = 64;
-constexpr int kRotRows = 256;          // 128 KiB of LDS
-constexpr int kAttendManyRows = 4096;
+constexpr int kRotRows = 256;          // 128 KiB of LDS, fewer beside a large B_q
+constexpr int kAttendHeadRows = 64;
+constexpr int kAttendManyRows = 1536;
 constexpr int kAttendRowsMaxCap = 1 << 22;  // a head's keys within 32-bit byte offsets
 
 // v of lane N of this lane's row of 16
@@ -4303,15 +4312,28 @@ __device__ __forceinline__ void static_for(F&& f) {
 // grid (work-groups resident at once, at most one per 16 rows), block 1024.
 // Work-group w (in XCD order, so that the rows of a KV group meet in one L2)
 // takes rows [w * per_group, (w + 1) * per_group), its waves one each in turn.
-template <bool KBF>
+// 16 codes of 16 dims fill half of an MFMA's 32; the other half is zero.
+template <int RK>
+constexpr int attend_bq_bytes() { return (RK + 31) / 32 * 8 * 3 * kWave * 16; }
+template <bool RECON, int RK>
+constexpr int attend_rot_rows() {
+  return RECON ? std::min(kRotRows, (160 * 1024 - attend_bq_bytes<RK>()) / 512) : kRotRows;
+}
+template <int RK, bool KBF, int ST, bool RECON>
 __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
-    const void* __restrict__ keys, const float* __restrict__ values, int H_q, int H_kv, int N_cap,
-    int N_valid, const float* __restrict__ q, const int* __restrict__ q_pos, int Q,
+    const void* __restrict__ keys, const float* __restrict__ values, const uint8_t* __restrict__ index,
+    int n_tiles, int H_q, int H_kv, int index_heads, int N_cap, int N_valid, const float* __restrict__ q,
+    const int* __restrict__ q_pos, int Q, const float* __restrict__ Bq, const float* __restrict__ mu,
     const int* __restrict__ top_idx, int k, float log_theta, int n_rows, int per_group, int groups,
     int n_hi, float* __restrict__ out) {
   constexpr int D = saki::kHeadDim;
   constexpr int HALF = D / 2;
-  __shared__ __align__(16) float rot[kRotRows][D];  // cosines of pairs 0 .. 63, then sines
+  constexpr int ES = code_bytes<ST>();
+  constexpr size_t TB = (size_t)kTile * RK * ES;
+  constexpr int NK = (RK + 31) / 32;  // MFMA steps of 32 code dims
+  __shared__ __align__(16) float rot[attend_rot_rows<RECON, RK>()][D];  // cosines of pairs 0 .. 63, then sines
+  // term p of B_q[dim(mb, qi)][32 kk + 8 g .. + 7], dim(mb, qi) = 64 (mb / 4) + 4 qi + mb % 4
+  __shared__ uint4 bqs[RECON ? NK : 1][RECON ? 8 : 1][RECON ? 3 : 1][RECON ? kWave : 1];
   const long long lg = xcd_logical_block(groups);
   if (lg < 0) return;  // uniform over the work-group
   {
@@ -4330,9 +4352,40 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
   const int r_end = (int)min((long long)n_rows, (lg + 1) * per_group);
   const int steps = (k + 15) / 16;
   const int my_e = 16 * (qi >> 2) + 4 * g + (qi & 3);  // this lane's list entry
-  for (int row = (int)(lg * per_group) + wave; row < r_end; row += kAttendRowWaves) {
-    const int bh = row / Q, i = row % Q;
-    const size_t kv = (size_t)(bh / H_q) * H_kv + (bh % H_q) / (H_q / H_kv);
+  // the rows of one head at a time (uniform over the work-group)
+  for (int seg = (int)(lg * per_group), seg_end; seg < r_end; seg = seg_end) {
+  const int bh = seg / Q, h = bh % H_q;
+  seg_end = min(r_end, (bh + 1) * Q);
+  const size_t kv = (size_t)(bh / H_q) * H_kv + h / (H_q / H_kv);
+  const uint8_t* cb = index + ((size_t)(bh / H_q) * index_heads + h / (H_q / index_heads)) * n_tiles * TB;
+  float m0[4], m1[4];
+  if constexpr (RECON) {
+    __syncthreads();  // the previous head's reads are done
+    for (int e = threadIdx.x; e < NK * 8 * kWave; e += kAttendRowWaves * kWave) {
+      const int l = e % kWave, mb = e / kWave % 8, kk = e / kWave / 8;
+      const int d = HALF * (mb / 4) + 4 * (l % 16) + mb % 4, c = 32 * kk + 8 * (l / 16);
+      float4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+      if (c < RK) {
+        const float* src = Bq + ((size_t)h * D + d) * RK + c;
+        x = *reinterpret_cast<const float4*>(src);
+        y = *reinterpret_cast<const float4*>(src + 4);
+      }
+      uint32_t t[4][3];
+      split3_bf16x2(x.x, x.y, t[0]);
+      split3_bf16x2(x.z, x.w, t[1]);
+      split3_bf16x2(y.x, y.y, t[2]);
+      split3_bf16x2(y.z, y.w, t[3]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) bqs[kk][mb][p][l] = uint4{t[0][p], t[1][p], t[2][p], t[3][p]};
+    }
+    const float4 x = *reinterpret_cast<const float4*>(mu + (kv % H_kv) * D + 4 * qi);
+    const float4 y = *reinterpret_cast<const float4*>(mu + (kv % H_kv) * D + HALF + 4 * qi);
+    m0[0] = x.x; m0[1] = x.y; m0[2] = x.z; m0[3] = x.w;
+    m1[0] = y.x; m1[1] = y.y; m1[2] = y.z; m1[3] = y.w;
+    __syncthreads();
+  }
+  for (int row = seg + wave; row < seg_end; row += kAttendRowWaves) {
+    const int i = row - bh * Q;
     const char* kb = reinterpret_cast<const char*>(keys) + kv * N_cap * D * (KBF ? 2 : 4);
     const char* vb = reinterpret_cast<const char*>(values + kv * N_cap * D);
     int my_j = my_e < k ? top_idx[(size_t)row * k + my_e] : -1;
@@ -4344,30 +4397,11 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
     // a skipped entry reads row 0 and gets weight 0
     const uint32_t j_c = (uint32_t)max(my_j, 0);
     float my_s = -INFINITY;
-    static_for<4>([&](auto bc) {
+    // scores of step b's keys (dims 4 qi + e in k0, 64 + 4 qi + e in k1)
+    auto scores = [&](auto bc, const float (&k0)[4][4], const float (&k1)[4][4]) {
       constexpr int b = decltype(bc)::value;
-      if (b >= steps) return;
-      float k0[4][4], k1[4][4];
       uint32_t jv[4];
-      static_for<4>([&](auto vc) {
-        constexpr int v = decltype(vc)::value;
-        jv[v] = row_bcast_u32<4 * b + v>(j_c);
-        if constexpr (KBF) {
-          const uint32_t off = jv[v] * (uint32_t)(D * 2) + (uint32_t)(8 * qi);
-          const uint2 x = *reinterpret_cast<const uint2*>(kb + off);
-          const uint2 y = *reinterpret_cast<const uint2*>(kb + off + D);
-          k0[v][0] = __uint_as_float(x.x << 16); k0[v][1] = __uint_as_float(x.x & 0xffff0000u);
-          k0[v][2] = __uint_as_float(x.y << 16); k0[v][3] = __uint_as_float(x.y & 0xffff0000u);
-          k1[v][0] = __uint_as_float(y.x << 16); k1[v][1] = __uint_as_float(y.x & 0xffff0000u);
-          k1[v][2] = __uint_as_float(y.y << 16); k1[v][3] = __uint_as_float(y.y & 0xffff0000u);
-        } else {
-          const uint32_t off = jv[v] * (uint32_t)(D * 4) + (uint32_t)(16 * qi);
-          const float4 x = *reinterpret_cast<const float4*>(kb + off);
-          const float4 y = *reinterpret_cast<const float4*>(kb + off + HALF * 4);
-          k0[v][0] = x.x; k0[v][1] = x.y; k0[v][2] = x.z; k0[v][3] = x.w;
-          k1[v][0] = y.x; k1[v][1] = y.y; k1[v][2] = y.z; k1[v][3] = y.w;
-        }
-      });
+      static_for<4>([&](auto vc) { jv[decltype(vc)::value] = row_bcast_u32<4 * b + decltype(vc)::value>(j_c); });
       float sc[4];
       const uint32_t reach = (uint32_t)(n_hi * kRotLo);
       bool far = false;
@@ -4412,6 +4446,106 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
       }
 #pragma unroll
       for (int v = 0; v < 4; ++v) my_s = qi == 4 * b + v ? sc[v] : my_s;
+    };
+    if constexpr (!RECON) static_for<4>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if (b >= steps) return;
+      float k0[4][4], k1[4][4];
+      static_for<4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const uint32_t jv = row_bcast_u32<4 * b + v>(j_c);
+        if constexpr (KBF) {
+          const uint32_t off = jv * (uint32_t)(D * 2) + (uint32_t)(8 * qi);
+          const uint2 x = *reinterpret_cast<const uint2*>(kb + off);
+          const uint2 y = *reinterpret_cast<const uint2*>(kb + off + D);
+          k0[v][0] = __uint_as_float(x.x << 16); k0[v][1] = __uint_as_float(x.x & 0xffff0000u);
+          k0[v][2] = __uint_as_float(x.y << 16); k0[v][3] = __uint_as_float(x.y & 0xffff0000u);
+          k1[v][0] = __uint_as_float(y.x << 16); k1[v][1] = __uint_as_float(y.x & 0xffff0000u);
+          k1[v][2] = __uint_as_float(y.y << 16); k1[v][3] = __uint_as_float(y.y & 0xffff0000u);
+        } else {
+          const uint32_t off = jv * (uint32_t)(D * 4) + (uint32_t)(16 * qi);
+          const float4 x = *reinterpret_cast<const float4*>(kb + off);
+          const float4 y = *reinterpret_cast<const float4*>(kb + off + HALF * 4);
+          k0[v][0] = x.x; k0[v][1] = x.y; k0[v][2] = x.z; k0[v][3] = x.w;
+          k1[v][0] = y.x; k1[v][1] = y.y; k1[v][2] = y.z; k1[v][3] = y.w;
+        }
+      });
+      scores(bc, k0, k1);
+    });
+    // reconstruction, two steps (32 keys) for each read of B_q
+    if constexpr (RECON) static_for<2>([&](auto pc) {
+      constexpr int p2 = 2 * decltype(pc)::value;
+      if (p2 >= steps) return;
+      f32x4_t acc[2][8];
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) acc[s2][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      // lane (qi, g): code dims 32 kk + 8 g .. + 7 of list entry 16 b + qi
+      const uint8_t* src[2];
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const uint32_t j = (uint32_t)__shfl((int)j_c, 16 * ((qi >> 2) & 3) + 4 * (p2 + s2) + (qi & 3), kWave);
+        src[s2] = cb + (size_t)(j / kTile) * TB + (size_t)(j % kTile) * 16;
+      }
+#pragma unroll 1
+      for (int kk = 0; kk < NK; ++kk) {
+        const bool in = 32 * kk + 8 * g < RK;  // RK = 16: lane groups 2 and 3 hold zeros
+        const int c = in ? 32 * kk + 8 * g : 0;
+        bf16x8_t cv[2][ST == kStF32 ? 3 : 1];
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          if constexpr (ST == kStF32) {
+            const uint4 x = *reinterpret_cast<const uint4*>(src[s2] + (size_t)(c / 4) * kTile * 16);
+            const uint4 y = *reinterpret_cast<const uint4*>(src[s2] + (size_t)(c / 4 + 1) * kTile * 16);
+            float f[8];
+            unpack_piece<false>(x, f);
+            unpack_piece<false>(y, f + 4);
+            uint32_t t[4][3];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) split3_bf16x2(in ? f[2 * e] : 0.f, in ? f[2 * e + 1] : 0.f, t[e]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) cv[s2][p] = as_bf16x8(uint4{t[0][p], t[1][p], t[2][p], t[3][p]});
+          } else if constexpr (ST == kStBf16) {
+            const uint4 x = *reinterpret_cast<const uint4*>(src[s2] + (size_t)(c / 8) * kTile * 16);
+            cv[s2][0] = as_bf16x8(in ? x : uint4{0u, 0u, 0u, 0u});
+          } else {
+            const uint2 x = *reinterpret_cast<const uint2*>(src[s2] + (size_t)(c / 16) * kTile * 16 + c % 16);
+            const uint2 w0 = e4m3x4_to_bf16(in ? x.x : 0u), w1 = e4m3x4_to_bf16(in ? x.y : 0u);
+            cv[s2][0] = as_bf16x8(uint4{w0.x, w0.y, w1.x, w1.y});
+          }
+        }
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) {
+          const bf16x8_t w1 = as_bf16x8(bqs[kk][mb][0][lane]), w2 = as_bf16x8(bqs[kk][mb][1][lane]),
+                         w3 = as_bf16x8(bqs[kk][mb][2][lane]);
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) {
+            f32x4_t a = acc[s2][mb];
+            if constexpr (ST == kStF32) {
+              a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][2], w1, a, 0, 0, 0);
+              a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][1], w2, a, 0, 0, 0);
+            }
+            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][0], w3, a, 0, 0, 0);
+            if constexpr (ST == kStF32) a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][1], w1, a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][0], w2, a, 0, 0, 0);
+            acc[s2][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[s2][0], w1, a, 0, 0, 0);
+          }
+        }
+      }
+      static_for<2>([&](auto sc2) {
+        constexpr int s2 = decltype(sc2)::value;
+        if (p2 + s2 >= steps) return;
+        float k0[4][4], k1[4][4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            k0[v][e] = m0[e] + acc[s2][e][v];
+            k1[v][e] = m1[e] + acc[s2][4 + e][v];
+          }
+        scores(std::integral_constant<int, p2 + s2>{}, k0, k1);
+      });
     });
     // softmax over the row's entries, one per lane
     my_s = my_j >= 0 ? my_s * (1.f / 11.313708498984761f) : -INFINITY;
@@ -4443,6 +4577,7 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
     float* op = out + (size_t)row * D + 4 * qi;
     if (g == 0) *reinterpret_cast<float4*>(op) = float4{o0[0], o0[1], o0[2], o0[3]};
     if (g == 1) *reinterpret_cast<float4*>(op + HALF) = float4{o1[0], o1[1], o1[2], o1[3]};
+  }
   }
 }
 
@@ -4478,21 +4613,27 @@ void launch_attend(const void* keys, const float* values, const uint8_t* index, 
                    const int* q_pos, int Q, const float* Bq, const float* mu, const int* top_idx,
                    int k, float rope_theta, float* out, hipStream_t s) {
   const size_t rows = (size_t)B * H_q * Q;
-  if constexpr (!RECON) {
-    // 16-byte loads of keys, values, queries and the output; a head's keys
-    // within 32-bit offsets
-    const bool al = ((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(values) |
-                      reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    const int slots = resident_groups(attend_rows_kernel<KBF>, kAttendRowWaves * kWave);
-    if (al && slots > 0 && rows >= (size_t)kAttendManyRows && rows <= 0x7fffffffu &&
-        N_cap <= kAttendRowsMaxCap) {
-      const int per = std::max(kAttendRowWaves, (int)((rows + slots - 1) / slots));
-      const int groups = (int)((rows + per - 1) / per);
-      const int n_hi = std::min(kRotRows - kRotLo, (N_valid + kRotLo - 1) / kRotLo);
-      hipLaunchKernelGGL((attend_rows_kernel<KBF>), dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)),
-                         dim3(kAttendRowWaves * kWave), 0, s, keys, values, H_q, H_kv, N_cap, N_valid, q,
-                         q_pos, Q, top_idx, k, logf(rope_theta), (int)rows, per, groups, n_hi, out);
-      return;
+  {
+    // 16-byte loads of keys (or B_q and mu), values, queries and the output; a
+    // head's rows within 32-bit byte offsets
+    const uintptr_t src = RECON ? reinterpret_cast<uintptr_t>(Bq) | reinterpret_cast<uintptr_t>(mu)
+                                : reinterpret_cast<uintptr_t>(keys);
+    const bool al = ((src | reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(q) |
+                      reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+    if (al && rows >= (size_t)kAttendManyRows && rows <= 0x7fffffffu && N_cap <= kAttendRowsMaxCap &&
+        (!RECON || Q >= kAttendHeadRows)) {
+      const int slots = resident_groups(attend_rows_kernel<RK, KBF, ST, RECON>, kAttendRowWaves * kWave);
+      if (slots > 0) {
+        const int per = std::max(kAttendRowWaves, (int)((rows + slots - 1) / slots));
+        const int groups = (int)((rows + per - 1) / per);
+        const int n_hi = std::min(attend_rot_rows<RECON, RK>() - kRotLo, (N_valid + kRotLo - 1) / kRotLo);
+        hipLaunchKernelGGL((attend_rows_kernel<RK, KBF, ST, RECON>),
+                           dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)), dim3(kAttendRowWaves * kWave),
+                           0, s, keys, values, index, (int)saki::n_tiles(N_cap), H_q, H_kv, index_heads, N_cap,
+                           N_valid, q, q_pos, Q, Bq, mu, top_idx, k, logf(rope_theta), (int)rows, per, groups, n_hi,
+                           out);
+        return;
+      }
     }
   }
   dim3 grid((unsigned)Q, (unsigned)(B * H_q));

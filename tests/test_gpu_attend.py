@@ -213,3 +213,42 @@ def test_attend_many_rows(k, N, Q, far, keys_bf16):
         assert np.all(out[0, h, 5] == 0.0)
         _check(out[0, h, rows], q[0, h, rows], pos[rows], keys[0, h // 2], values[0, h // 2],
                visible[0, h, rows])
+
+
+@pytest.mark.parametrize("sketch", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("r,shared", [(16, False), (32, True), (64, False), (128, True)])
+def test_attend_many_rows_reconstructed(sketch, r, shared):
+    """1,536 rows and more: keys reconstructed on the MFMA, against float64
+    reconstruction from the exported codes (float32 factors); heads that begin
+    inside a work-group's rows, both index kinds, a list that is no multiple of
+    16 or 32 entries, positions past the table."""
+    rng = np.random.default_rng(r)
+    N, Q, H_q, H_kv, k = 900, 401, 4, 2, 41
+    keys = rng.standard_normal((1, H_kv, N, 128)).astype(np.float32)
+    values = rng.standard_normal((1, H_kv, N, 128)).astype(np.float32)
+    q = rng.standard_normal((1, H_q, Q, 128)).astype(np.float32)
+    sets = H_kv if shared else H_q
+    B_k = (rng.standard_normal((sets, 128, r)) / 11).astype(np.float32)
+    B_q = (rng.standard_normal((H_q, 128, r)) / r ** 0.5).astype(np.float32)
+    mu = rng.standard_normal((H_kv, 128)).astype(np.float32)
+    idx = np.stack([rng.permutation(N)[:k] for _ in range(H_q * Q)]).reshape(1, H_q, Q, k).astype(np.int32)
+    idx[0, :, 5] = -1
+    pos = rng.integers(0, N, Q).astype(np.int32)
+    pos[::7] += 30_000
+    index = S.saki_build_index(_t(keys), _t(B_k), _t(mu), r, sketch, sets)
+    codes = S.saki_index_export(index, sketch, 1, sets, N, r).double().cpu().numpy()
+    out = S.saki_attend(_t(values), _t(q), _t(idx, torch.int32), N, index=index, sketch=sketch, B_q=_t(B_q),
+                        mu=_t(mu), r=r, index_heads=sets, q_pos=_t(pos, torch.int32)).cpu().numpy()
+    rows = np.unique(np.concatenate([[0, 1, 7, 14, Q - 1], rng.integers(0, Q, 12)]))
+    rows = rows[rows != 5]
+    for h in range(H_q):
+        g = h // 2
+        w = B_q[h].astype(np.float64)
+        c = codes[0, g if shared else h]
+        khat = mu[g] + c @ w.T
+        # float32 sums: r products, 2^-24 each, of the absolute sums
+        dk = np.linalg.norm((np.abs(c) @ np.abs(w).T + np.abs(mu[g])) * r * 2.0 ** -24, axis=1)
+        qn = np.linalg.norm(q[0, h], axis=1)
+        extra = np.stack([qn[i] * dk[idx[0, h, i]] / np.sqrt(128) for i in rows])
+        assert np.all(out[0, h, 5] == 0.0)
+        _check(out[0, h, rows], q[0, h, rows], pos[rows], khat, values[0, g], idx[0, h, rows], extra)
