@@ -3029,7 +3029,7 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
   __shared__ float ss[kMR * kWave];      // float32 score of sorted entry a
   __shared__ float se[kMR * kWave];      // and its error radius
   __shared__ float tau_s[kMR];           // gates
-  __shared__ int bad_s[kMR];             // invalid lists
+  __shared__ int bad_s[kMR];             // 1: invalid lists, 2: rows of at most k keys
   __shared__ int ccount[kGateWaves][kMR];
   __shared__ int wg_fallback;
   __shared__ int bj_m[kGateWaves][kBatch];  // per wave: others' key, exact score, row
@@ -3088,8 +3088,21 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
       uint32_t key = lane < k ? (uint32_t)aj : (0x80000000u | (uint32_t)lane);
       wave_sort<KeysU32>(key);
       const uint32_t nxt = (uint32_t)__shfl_down((int)key, 1, kWave);
-      bad |= lane < kWave - 1 && key == nxt;
+      const bool dup = lane < kWave - 1 && key == nxt;
       sl[r * kWave + lane] = key;
+      if (!ordered && lim_r <= k) {
+        // every visible key is in T: the list's distinct visible keys count,
+        // and the row is done (gate +inf).  As a row without a gate, each of
+        // them would be rescored and ranked.
+        const int n = __popcll(__ballot(key < (uint32_t)lim_r && !dup));
+        if (lane == 0) {
+          hits[bh * Q + row0 + r] = n;
+          tau_s[r] = INFINITY;
+          bad_s[r] = 2;
+        }
+        continue;
+      }
+      bad |= dup;
       if (lane == 0) bad_s[r] = __ballot(bad) != 0;  // an invalid list keeps tau = -inf
     }
   }
@@ -3335,6 +3348,10 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
     for (; r_end < my_rows; ++r_end) {
       const int r = wave + kGateWaves * r_end;
       const bool rbad = bad_s[r] != 0;
+      if (bad_s[r] == 2) {  // counted already
+        if (lane == 0) boff[r_end - r_done] = boff[r_end - r_done + 1] = nb;
+        continue;
+      }
       // others of this row: all of C for an invalid list, else C minus S,
       // appended in one pass (entries past the batch are not written; a row
       // that does not fit is taken back and starts the next batch)
@@ -3392,6 +3409,7 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
       const size_t row = bh * Q + row0 + r;
       const float* qr = q + row * D;
       const bool rbad = bad_s[r] != 0;
+      if (bad_s[r] == 2) continue;
       const int o0 = boff[rr - r_done], o1 = boff[rr - r_done + 1];
       // lane a: sorted list entry a (pads, k < 64, have the top bit set)
       const uint32_t kj = sl[r * kWave + lane];
