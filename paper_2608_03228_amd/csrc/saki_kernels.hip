@@ -92,12 +92,15 @@ __device__ __forceinline__ uint32_t e4m3_bits(float x) {
 }
 
 // Four fp8 E4M3 codes (the bytes of w, lowest first) -> two words of bf16
-// pairs.  Exact: an E4M3 value has at most 4 significant bits.
+// pairs, one instruction each (through float32 it took six, which bound the
+// scoring of fp8 codes).  Exact: an E4M3 value has at most 4 significant bits.
 __device__ __forceinline__ uint2 e4m3x4_to_bf16(uint32_t w) {
-  const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);  // bytes 0, 1
-  const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);   // bytes 2, 3
-  return uint2{(__float_as_uint(lo[0]) >> 16) | (__float_as_uint(lo[1]) & 0xffff0000u),
-               (__float_as_uint(hi[0]) >> 16) | (__float_as_uint(hi[1]) & 0xffff0000u)};
+  const auto lo = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.f, false);  // bytes 0, 1
+  const auto hi = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.f, true);   // bytes 2, 3
+  uint2 r;
+  __builtin_memcpy(&r.x, &lo, sizeof(r.x));
+  __builtin_memcpy(&r.y, &hi, sizeof(r.y));
+  return r;
 }
 
 template <bool BF>

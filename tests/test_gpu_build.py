@@ -97,3 +97,17 @@ def test_short_ranges_one_head_per_work_group():
         _check(got[:, :, n0:n0 + cnt], keys64[:, :, n0:n0 + cnt], B_k, mu, "f32", H_q // H_kv)
         np.testing.assert_array_equal(got[:, :, :n0], before[:, :, :n0])
         np.testing.assert_array_equal(got[:, :, n0 + cnt:], before[:, :, n0 + cnt:])
+
+
+def test_every_fp8_code_widens_exactly():
+    """All finite E4M3 codes (subnormals and both zeros among them) through the
+    kernels' fp8 -> bf16 widening, as the export reads them."""
+    code = np.array([c for c in range(256) if c & 0x7F != 0x7F], np.uint8)
+    e, m = (code >> 3) & 15, code & 7
+    want = np.where(e == 0, m * 2.0 ** -9, (1 + m / 8) * 2.0 ** (e.astype(np.float64) - 7))
+    want = np.where(code & 0x80, -want, want)
+    N, r = 64, 16  # one tile: the index is its keys' 16-byte codes in order
+    raw = np.resize(code, N * r)
+    got = S.saki_index_export(torch.from_numpy(raw).to(DEV), "fp8", 1, 1, N, r).cpu().numpy()
+    np.testing.assert_array_equal(got.reshape(-1), np.resize(want, N * r))
+    assert np.array_equal(np.signbit(got.reshape(-1)), np.resize(code & 0x80, N * r) != 0)
