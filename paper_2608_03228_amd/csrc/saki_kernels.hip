@@ -3975,22 +3975,26 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void merge_kernel(
 
 // ---------------------------------------------------------------- calibration moments
 
-// grid: (H_q + H_kv) * nb * (nb + 1) / 2 work-groups, nb = ceil(d / 64), block
-// 256.  Work-group (head, block pair bi <= bj) forms the 64 x 64 block (rows
-// 64 bi.., columns 64 bj..) of that head's moment and writes it and its
-// mirror: thread (ty, tx) holds the 4 x 4 outputs of rows 64 bi + 4 ty ..,
-// columns 64 bj + 4 tx .., each a float64 sum over the tokens in order.
-// Heads below H_q are query heads (uncentred); the rest are KV heads, centred
-// by their column means, which every work-group computes for its own 128
-// columns.  Tokens are staged in LDS 32 at a time.
-constexpr int kMomBlk = 64;
-constexpr int kMomChunk = 32;  // tokens staged per step
+// grid: (H_q + H_kv) * nb * (nb + 1) / 2 work-groups, nb = ceil(d / 32), block
+// 256.  Work-group (head, block pair bi <= bj) forms the 32 x 32 block (rows
+// 32 bi.., columns 32 bj..) of that head's moment on the f64 MFMA (16x16x4: four
+// tokens a step) and writes it and its mirror.  Its four waves take a quarter
+// of the tokens each, their sums are added in wave order.  An operand is one
+// float per lane, loaded in coalesced 64-byte pieces kMomAhead steps ahead, so
+// nothing is staged.  Heads below H_q are query heads (uncentred); the rest are
+// KV heads, centred by their column means, which every work-group computes for
+// its own 64 columns.  As float64 FMAs over tokens staged in LDS, 64 x 64 a
+// work-group, 120 of them left more than half of the CUs idle: 77 us for
+// 40 heads of 512 tokens.
+constexpr int kMomBlk = 32;
+constexpr int kMomWaves = 4;
+constexpr int kMomAhead = 8;
 
-__global__ __launch_bounds__(256) void moments_kernel(const float* __restrict__ q_cal,
-                                                      const float* __restrict__ k_cal, int H_q,
-                                                      int T, int d, double* __restrict__ Sq,
-                                                      double* __restrict__ Sk,
-                                                      double* __restrict__ mu_out) {
+__global__ __launch_bounds__(kMomWaves * kWave) void moments_kernel(const float* __restrict__ q_cal,
+                                                                    const float* __restrict__ k_cal, int H_q,
+                                                                    int T, int d, double* __restrict__ Sq,
+                                                                    double* __restrict__ Sk,
+                                                                    double* __restrict__ mu_out) {
   const int nb = (d + kMomBlk - 1) / kMomBlk;
   const int npairs = nb * (nb + 1) / 2;
   const int head = blockIdx.x / npairs;
@@ -4003,82 +4007,99 @@ __global__ __launch_bounds__(256) void moments_kernel(const float* __restrict__ 
   const bool key = head >= H_q;
   const int hh = key ? head - H_q : head;
   const float* X = (key ? k_cal : q_cal) + (size_t)hh * T * d;
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
+  const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  const int qi = lane % 16, g = lane / 16;
   const int i0 = bi * kMomBlk, j0 = bj * kMomBlk;
-  __shared__ double xi[kMomChunk][kMomBlk], xj[kMomChunk][kMomBlk];
-  __shared__ double mean[2 * kMomBlk];
-  __shared__ double part[2][2 * kMomBlk];
-  // column means (KV heads): two threads per column, even and odd tokens
-  {
-    const int c = tid % (2 * kMomBlk), h = tid / (2 * kMomBlk);
+  constexpr int NC = 2 * kMomBlk;  // columns of both blocks
+  constexpr int TP = kMomWaves * kWave / NC;
+  __shared__ double mean[NC];
+  __shared__ double part[TP][NC];
+  __shared__ double red[kMomWaves][16][kWave];
+  // column means (KV heads): TP threads per column, every TP-th token each
+  if (key) {
+    const int c = tid % NC, h = tid / NC;
     const int col = c < kMomBlk ? i0 + c : j0 + c - kMomBlk;
     double m = 0.0;
-    if (key && col < d) {
+    if (col < d) {
 #pragma unroll 16
-      for (int t = h; t < T; t += 2) m += (double)X[(size_t)t * d + col];
+      for (int t = h; t < T; t += TP) m += (double)X[(size_t)t * d + col];
     }
     part[h][c] = m;
   }
   __syncthreads();
-  if (tid < 2 * kMomBlk) mean[tid] = key ? (part[0][tid] + part[1][tid]) / (double)T : 0.0;
-  __syncthreads();
-  double acc[4][4];
+  if (tid < NC) {
+    double m = 0.0;
+    if (key) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[a][e] = 0.0;
-  // tokens t0 .. t0 + 31 of both column blocks: element u of this thread is
-  // token t0 + (tid + 256 u) / 64, column (tid + 256 u) % 64; the next chunk's
-  // values are loaded while this one is summed
-  constexpr int kPer = kMomChunk * kMomBlk / 256;
-  float ni[kPer], nj[kPer];
-  auto load_chunk = [&](int t0) {
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + 256 * u, t = t0 + e / kMomBlk, c = e % kMomBlk;
-      ni[u] = (t < T && i0 + c < d) ? X[(size_t)t * d + i0 + c] : 0.f;
-      nj[u] = (t < T && j0 + c < d) ? X[(size_t)t * d + j0 + c] : 0.f;
+      for (int h = 0; h < TP; ++h) m += part[h][tid];
+      m /= (double)T;
     }
-  };
-  load_chunk(0);
-  for (int t0 = 0; t0 < T; t0 += kMomChunk) {
-    // stage the chunk (centred; 0 past T or d), then request the next one
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + 256 * u, tt = e / kMomBlk, c = e % kMomBlk, t = t0 + tt;
-      xi[tt][c] = (t < T && i0 + c < d) ? (double)ni[u] - mean[c] : 0.0;
-      xj[tt][c] = (t < T && j0 + c < d) ? (double)nj[u] - mean[kMomBlk + c] : 0.0;
-    }
-    if (t0 + kMomChunk < T) load_chunk(t0 + kMomChunk);
-    __syncthreads();
-#pragma unroll 4
-    for (int tt = 0; tt < kMomChunk; ++tt) {
-      double va[4], vb[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        va[a] = xi[tt][4 * ty + a];
-        vb[a] = xj[tt][4 * tx + a];
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[a][e] = fma(va[a], vb[e], acc[a][e]);
-    }
-    __syncthreads();
+    mean[tid] = m;
   }
+  __syncthreads();
+  // this lane's columns: i0 + qi, i0 + 16 + qi, j0 + qi, j0 + 16 + qi (the last
+  // column for those past d, whose products are not written); tokens t + g of
+  // a step, zero past the wave's last
+  const int steps = (T + 3) / 4, per = (steps + kMomWaves - 1) / kMomWaves;
+  const int s_beg = wave * per, s_end = min(steps, s_beg + per);
+  int col[4];
+  double mc[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int x = 16 * (c & 1) + qi;
+    col[c] = min((c < 2 ? i0 : j0) + x, d - 1);
+    mc[c] = mean[(c < 2 ? 0 : kMomBlk) + x];
+  }
+  f64x4_t acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) acc[a][e] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  float nx[kMomAhead][4];
+  auto load = [&](int st, float (&v)[4]) {
+    const size_t row = (size_t)min(4 * st + g, T - 1) * d;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = X[row + col[c]];
+  };
+#pragma unroll
+  for (int u = 0; u < kMomAhead; ++u) load(s_beg + u, nx[u]);
+  for (int s0 = s_beg; s0 < s_end; s0 += kMomAhead) {
+#pragma unroll
+    for (int u = 0; u < kMomAhead; ++u) {
+      const int st = s0 + u;
+      const bool ok = st < s_end && 4 * st + g < T;
+      double x[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[c] = ok ? (double)nx[u][c] - mc[c] : 0.0;
+      load(st + kMomAhead, nx[u]);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) acc[a][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a], x[2 + e], acc[a][e], 0, 0, 0);
+    }
+  }
+  // register v of tile (a, e): row i0 + 16 a + g + 4 v, column j0 + 16 e + qi
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][(2 * a + e) * 4 + v][lane] = acc[a][e][v];
+  __syncthreads();
   double* S = key ? Sk + (size_t)hh * d * d : Sq + (size_t)hh * d * d;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int u = 0; u < 16 / kMomWaves; ++u) {
+    const int x = wave * (16 / kMomWaves) + u;
+    double v = red[0][x][lane];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = i0 + 4 * ty + a, j = j0 + 4 * tx + e;
-      if (i < d && j < d) {
-        const double v = acc[a][e] / (double)T;
-        S[(size_t)i * d + j] = v;
-        S[(size_t)j * d + i] = v;
-      }
+    for (int w = 1; w < kMomWaves; ++w) v += red[w][x][lane];
+    v /= (double)T;
+    const int i = i0 + 16 * (x / 8) + g + 4 * (x % 4), j = j0 + 16 * (x / 4 % 2) + qi;
+    if (i < d && j < d) {
+      S[(size_t)i * d + j] = v;
+      S[(size_t)j * d + i] = v;
     }
+  }
   if (key && bi == 0 && tid < kMomBlk && j0 + tid < d) mu_out[(size_t)hh * d + j0 + tid] = mean[kMomBlk + tid];
 }
 
