@@ -536,7 +536,7 @@ def run_decode(spec, r, sk, k, steps, warmup, shared=False, attend=True, cpu=Fal
         kern = "score_scan_kernel" if N >= 16384 else "score_batch_kernel"
         inst = f"{kern}<{r}, {st}>"
     else:
-        kern = "score_stream_kernel"
+        kern = "score_decode_kernel"
         inst = f"{kern}<{r}, {st}, {4 if (H_q // IH) * Q >= 4 else 1}>"
     roof["traffic"] = measured_traffic(kern, spec.name, inst)
     roof["kernel"] = "score_topk"

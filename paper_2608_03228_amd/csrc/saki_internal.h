@@ -41,7 +41,6 @@ struct Plan {
   int rows = 1;        // query rows per wave
   int waves = 1;       // waves per workgroup
   int row_blocks = 0;  // workgroups along the query axis
-  bool split = false;  // streaming: the waves of a workgroup share rows and take consecutive chunks
   bool scan = false;   // MFMA rows scored in one pass (row_blocks: 16-row blocks, one per wave;
                        // with a split key axis z_off: chunk gates, flag_off: rows to redo)
   int chunk = kTile;   // keys per chunk (multiple of 64)
@@ -86,7 +85,8 @@ inline Plan make_plan(int B, int heads, int Q, int N_valid, int part_entry_bytes
 // Score path: the workspace holds the partial lists of a split key axis
 // (float score + int index), at least 256 bytes so that a size of 0 keeps
 // meaning invalid arguments.  The MFMA kernels take 16 queries of one head per
-// wave (the one-pass kernel when the rows are long); the streaming kernel
+// wave (the one-pass kernel when the rows are long); the decode kernel (whose
+// launch makes the chunks longer, never more)
 // takes the rows of one code set: the H_q / index_heads heads sharing it,
 // times Q.  The two-pass MFMA kernel reads the query sketches z (r values per
 // row: bf16 for bf16 and fp8 codes (dtype 1, 2), float32 for float32 codes)
@@ -123,8 +123,7 @@ inline Plan score_plan(int B, int H_q, int index_heads, int Q, int N_valid, int 
     p.ws_bytes = round_up(p.b_off + rows_total * sizeof(float), 256);
   }
   const int wave_rows = (int)((H_q / index_heads) * (size_t)Q + p.rows - 1) / p.rows;
-  if (!mfma && wave_rows < 4) {  // too few rows to fill a workgroup: its waves split the keys
-    p.split = true;
+  if (!mfma && wave_rows < 4) {
     p.waves = 4;
     p.row_blocks = wave_rows < 1 ? 1 : wave_rows;
   }
