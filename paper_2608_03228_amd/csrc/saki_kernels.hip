@@ -862,10 +862,10 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    // at or above the gate: above the next float below it; scores of -inf never
-    const float below = thr[r] == -INFINITY ? -INFINITY : unord_f32(ord_f32(thr[r]) - 1u);
+    // at or above the gate, compared as floats (a gate of +0 takes every zero); scores of -inf never
+    const float least = thr[r] == -INFINITY ? -__FLT_MAX__ : thr[r];
 #pragma unroll
-    for (int i = 0; i < T; ++i) append(r, s[i][r] > below, s[i][r], t_first + i * W * kTile + lane);
+    for (int i = 0; i < T; ++i) append(r, s[i][r] >= least, s[i][r], t_first + i * W * kTile + lane);
   }
 
   // ---- the tail

@@ -101,3 +101,35 @@ def test_decode_candidates_that_overflow(order):
         assert np.all(sc == sc[..., :1])
     else:
         _check(keys, q, 32, "f32", shared=True)
+
+
+# one, two and four rows a work-group; one chunk and several
+@pytest.mark.parametrize("N", [1500, 40_001])
+@pytest.mark.parametrize("Q,H_q,shared", [(1, 2, False), (2, 2, False), (1, 4, True)])
+def test_decode_scores_of_zero(N, Q, H_q, shared):
+    """A zero query (every score +0: the first 64 keys), and a cache of zero
+    keys with 40 that score above them and 100 below (the 64th best is 0)."""
+    g = torch.Generator(device=DEV).manual_seed(N)
+    base = torch.randn(D, generator=g, device=DEV)
+    at = torch.randperm(N, generator=g, device=DEV)
+    keys = torch.zeros((1, 1, N, D), device=DEV)
+    keys[0, 0, at[:40]] = torch.linspace(1, 5, 40, device=DEV)[:, None] * base
+    keys[0, 0, at[40:140]] = -torch.linspace(1, 5, 100, device=DEV)[:, None] * base
+    q = base.expand(1, H_q, Q, D).contiguous()
+    for sketch in ("f32", "bf16"):
+        idx, sc, _, _ = _run(keys, torch.zeros_like(q), 32, sketch, shared=shared)
+        assert np.array_equal(idx, np.broadcast_to(np.arange(64), idx.shape)) and np.all(sc == 0.0)
+        for sign in (1, -1):  # B_q and B_k are random: either sign of the query has 40 or 100 above 0
+            idx, sc, codes, B_q = _run(keys, sign * q, 32, sketch, shared=shared)
+            for h in range(H_q):
+                z = sign * q[0, h].double() @ B_q[h].double()
+                if sketch == "bf16":
+                    z = z.float().bfloat16().double()
+                s = (z @ codes[0, 0 if shared else h].T).cpu().numpy()
+                for i in range(Q):
+                    up = sc[0, h, i] > 0  # no key near the others': only ties within a code's rounding
+                    n = int((s[i] > 0).sum())
+                    assert up.sum() == min(64, n) and np.all(s[i, idx[0, h, i][up]] > 0)
+                    if n < 64:
+                        zero = np.flatnonzero(s[i] == 0)[:64 - n]
+                        assert np.array_equal(idx[0, h, i, n:], zero) and np.all(sc[0, h, i, n:] == 0.0)
