@@ -165,8 +165,8 @@ constexpr int kOnceWaves = 4096;    // waves wanted over the whole GPU
 constexpr int kOnceMaxRows = 2048;  // rows of 16 or more queries a head that take it
 inline OncePlan recall_once_plan(int B, int H_q, int H_kv, int Q, int N_valid) {
   OncePlan o;
+  if (Q <= 0 || N_valid <= 0) return o;  // no rows, or none with a key
   const Plan p = recall_plan(B, H_q, H_kv, Q, N_valid);
-  if (N_valid <= 0) return o;
   // The decision rescores every listed key (0.1 us a row) where the other path
   // rescores a few: 16 queries over 4,096 keys (512 rows) 59 us against 97,
   // over 262,144 keys 297 against 1,542; 17,536 rows over 4,096 keys 1,404

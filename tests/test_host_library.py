@@ -315,6 +315,9 @@ def test_size_helpers():
     assert S.saki_score_topk_workspace_bytes(1, 32, 1, 1 << 20, 32, 64, "bf16") > 32 * 64 * 8
     assert S.saki_recall_workspace_bytes(1, 32, 8, 1, 1 << 20, 128, 64) > 0
     assert S.saki_recall_workspace_bytes(1, 32, 8, 1, 1 << 20, 64, 64) == 0
+    # an empty batch needs nothing
+    assert S.saki_recall_workspace_bytes(1, 32, 8, 0, 1 << 20, 128, 64) == 0
+    assert S.saki_recall_workspace_bytes(1, 32, 8, 0, 0, 128, 64) == 0
 
 
 def test_scan_workspace_holds_lists_gates_and_flags():
