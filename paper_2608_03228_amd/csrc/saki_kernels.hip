@@ -848,9 +848,9 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     uint32_t* mx = reinterpret_cast<uint32_t*>(area);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      float m = s[0][r];
+      float m = -INFINITY;  // a lane whose scores are no numbers has no part in the gate
 #pragma unroll
-      for (int i = 1; i < T; ++i) m = fmaxf(m, s[i][r]);
+      for (int i = 0; i < T; ++i) m = fmaxf(m, s[i][r]);
       uint32_t o = ord_f32(m);
       wave_sort<KeysU32>(o);
       mx[(r * W + wave) * kWave + lane] = o;

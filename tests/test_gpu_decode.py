@@ -133,3 +133,26 @@ def test_decode_scores_of_zero(N, Q, H_q, shared):
                     if n < 64:
                         zero = np.flatnonzero(s[i] == 0)[:64 - n]
                         assert np.array_equal(idx[0, h, i, n:], zero) and np.all(sc[0, h, i, n:] == 0.0)
+
+
+@pytest.mark.parametrize("sketch", ["f32", "bf16"])
+@pytest.mark.parametrize("H_q,shared", [(1, False), (4, True)])
+def test_decode_scores_that_are_no_numbers(sketch, H_q, shared):
+    """NaN codes in half the lanes of every tile are never listed and do not
+    displace what is: the lists are those of an index with codes of 0 there."""
+    N, r = 16_000, 32
+    g = torch.Generator(device=DEV).manual_seed(4)
+    keys = torch.randn((1, 1, N, D), generator=g, device=DEV)
+    q = torch.randn((1, H_q, 1, D), generator=g, device=DEV)
+    B_k = torch.randn((1, D, r), generator=g, device=DEV) / D ** 0.5
+    B_q = torch.randn((H_q, D, r), generator=g, device=DEV) / D ** 0.5
+    mu = torch.zeros((1, D), device=DEV)
+    index = S.saki_build_index(keys, B_k, mu, r, sketch, 1)
+    tiles = (index.view(torch.float32).view(-1, r // 4, 64, 4) if sketch == "f32" else
+             index.view(torch.bfloat16).view(-1, r // 8, 64, 8))  # pieces of 16 bytes, 64 keys
+    out = []
+    for fill in (float("nan"), 0.0):
+        tiles[:, :, :32] = fill
+        out += S.saki_score_topk(index, sketch, q, B_q, mu, 1, N, N, r, index_heads=1 if shared else H_q)
+    assert (out[2] % 64 >= 32).all() and (out[3] > 0).all()
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
