@@ -19,7 +19,7 @@ constexpr int kBatchWaves = 1;         // its waves per work-group (16 rows each
 inline bool rank_supported(int r) { return r == 16 || r == 32 || r == 64 || r == 128; }
 // bytes per code element: float32 (0), bf16 (1), fp8 E4M3 (2)
 inline int elem_bytes(int dtype) { return dtype == 2 ? 1 : dtype == 1 ? 2 : 4; }
-inline size_t n_tiles(int N) { return ((size_t)N + kTile - 1) / kTile; }
+constexpr size_t n_tiles(int N) { return ((size_t)N + kTile - 1) / kTile; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Index layout, per (sequence b, query head h): tiles of 64 keys; inside a

@@ -616,12 +616,13 @@ __device__ __forceinline__ void merge_tree(typename KO::K* m, int stride, int n,
 }
 
 // grid: 1-D, xcd_logical_block order over (code set of a sequence, chunk, row
-// group), row groups fastest (they read the same codes), block 1024.
+// group), row groups fastest (they read the same codes), block 64 W.  The loops
+// count tiles: steps past the last of up to 2^31 - 1 keys do not fit an int.
 template <int RK, int ST, int R>
 __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     const uint8_t* __restrict__ index, int n_tiles, int N_valid, int Q,
     const int* __restrict__ q_pos, const float* __restrict__ q, const float* __restrict__ Bq,
-    const float* __restrict__ mu, int H_q, int H_kv, int gq, int n_bi, int row_groups, int chunk,
+    const float* __restrict__ mu, int H_q, int H_kv, int gq, int n_bi, int row_groups, int chunk_tiles,
     int n_chunks, int k, int* __restrict__ top_idx, float* __restrict__ top_score,
     uint64_t* __restrict__ part) {
   constexpr int ES = code_bytes<ST>();
@@ -663,8 +664,7 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     lim[r] = ok ? row_limit(i, Q, N_valid, q_pos) : 0;
     kmax = max(kmax, lim[r]);
   }
-  const int kbeg = ch * chunk;
-  const int kend = min(kbeg + chunk, kmax);
+  const int tbeg = ch * chunk_tiles, tend = min(tbeg + chunk_tiles, (int)saki::n_tiles(kmax));
   const uint8_t* hbase = index + bi * n_tiles * TB;
   // a tile's pieces are loaded two tiles ahead of their use (up to 64 bytes per
   // key, 128 where the registers allow; wider codes are loaded as they are used)
@@ -674,19 +674,19 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
   struct Raw {
     uint4 v[PF ? PF : 1];
   };
-  auto tile_ptr = [&](int t0) { return hbase + (size_t)(t0 / kTile) * TB + (size_t)lane * 16; };
-  auto load = [&](int t0, Raw& x) {
+  auto tile_ptr = [&](int t) { return hbase + (size_t)t * TB + (size_t)lane * 16; };
+  auto load = [&](int t, Raw& x) {
     if constexpr (PF > 0) {
-      if (t0 >= kend) return;
-      const uint8_t* tb = tile_ptr(t0);
+      if (t >= tend) return;
+      const uint8_t* tb = tile_ptr(t);
 #pragma unroll
       for (int p = 0; p < PF; ++p) x.v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)p * kTile * 16);
     }
   };
-  const int t_first = kbeg + wave * kTile;
+  const int t_first = tbeg + wave;
   Raw ra, rb;
   load(t_first, ra);
-  load(t_first + W * kTile, rb);
+  load(t_first + W, rb);
 
   // ---- the query sketch
   {
@@ -753,8 +753,8 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
 #pragma unroll
   for (int r = 0; r < R; ++r) bb[r] = zs[r][RK];
 
-  // scores of this lane's key of tile t0 (-inf past a row's limit)
-  auto score = [&](int t0, const Raw& x, float* out) {
+  // scores of this lane's key of tile t < tend (-inf past a row's limit)
+  auto score = [&](int t, const Raw& x, float* out) {
     float acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.f;
@@ -799,7 +799,7 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
       // least two rounds (a loop that is not unrolled, so that z is not kept)
       constexpr int PZ = std::min(64 / (R * (ST == kStFp8 ? 8 : 4)), NP / 2);
       constexpr int PB = kScalarZ ? std::min(NP, 8) : std::max(PZ, 1);
-      const uint8_t* tb = tile_ptr(t0);
+      const uint8_t* tb = tile_ptr(t);
       auto batch = [&](int p0) {
         uint4 v[PB];
 #pragma unroll
@@ -815,27 +815,27 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
         for (int p0 = 0; p0 < NP; p0 += PB) batch(p0);
       }
     }
-    const int j = t0 + lane;
+    const int j = t * kTile + lane;
 #pragma unroll
     for (int r = 0; r < R; ++r) out[r] = j < lim[r] ? acc[r] + bb[r] : -INFINITY;
   };
-  auto append = [&](int r, bool take, float sv, int j) {
+  auto append = [&](int r, bool take, float sv, int t) {
     const uint64_t mask = __ballot(take);
     if (mask == 0) return;
     int at = 0;
     if (lane == 0) at = atomicAdd(&cnt[r], __popcll(mask));
     at = __builtin_amdgcn_readfirstlane(at) + prefix_count(mask);
-    if (take && at < CAP) buf[r][at] = KO::make(sv, j);
+    if (take && at < CAP) buf[r][at] = KO::make(sv, t * kTile + lane);
   };
 
   // ---- the head
   float s[T][R];
 #pragma unroll
   for (int i = 0; i < T; ++i) {
-    const int t0 = t_first + i * W * kTile;
-    if (t0 < kend) {
-      score(t0, (i & 1) ? rb : ra, s[i]);
-      load(t0 + 2 * W * kTile, (i & 1) ? rb : ra);
+    const int t = t_first + i * W;
+    if (t < tend) {
+      score(t, (i & 1) ? rb : ra, s[i]);
+      load(t + 2 * W, (i & 1) ? rb : ra);
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) s[i][r] = -INFINITY;
@@ -844,7 +844,7 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
   float thr[R];  // the gate (-inf: every key is a candidate)
 #pragma unroll
   for (int r = 0; r < R; ++r) thr[r] = -INFINITY;
-  if (kend - kbeg > CAP) {
+  if (tend - tbeg > CAP / kTile) {
     uint32_t* mx = reinterpret_cast<uint32_t*>(area);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -865,16 +865,16 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     // at or above the gate, compared as floats (a gate of +0 takes every zero); scores of -inf never
     const float least = thr[r] == -INFINITY ? -__FLT_MAX__ : thr[r];
 #pragma unroll
-    for (int i = 0; i < T; ++i) append(r, s[i][r] >= least, s[i][r], t_first + i * W * kTile + lane);
+    for (int i = 0; i < T; ++i) append(r, s[i][r] >= least, s[i][r], t_first + i * W);
   }
 
   // ---- the tail
-  auto tail = [&](int t0, Raw& x) {
+  auto tail = [&](int t, Raw& x) {
     float v[R];
-    score(t0, x, v);
-    load(t0 + 2 * W * kTile, x);
+    score(t, x, v);
+    load(t + 2 * W, x);
 #pragma unroll
-    for (int r = 0; r < R; ++r) append(r, v[r] > thr[r], v[r], t0 + lane);
+    for (int r = 0; r < R; ++r) append(r, v[r] > thr[r], v[r], t);
   };
   // the row's candidates -> sorted, the best 64 first (every wave takes part)
   auto most_candidates = [&]() {
@@ -894,13 +894,13 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     __syncthreads();
     merge_tree<KO, R>(&buf[0][0], CAP / kWave, segs, wave, W, lane);
   };
-  const int head = W * T * kTile, round = W * kDecodeRound * kTile;
-  for (int r0 = kbeg + head; r0 < kend; r0 += round) {
-    for (int t0 = r0 + wave * kTile; t0 < min(kend, r0 + round); t0 += 2 * W * kTile) {
-      tail(t0, ra);
-      if (t0 + W * kTile < kend) tail(t0 + W * kTile, rb);
+  const int round = W * kDecodeRound;
+  for (int r0 = tbeg + W * T; r0 < tend; r0 += round) {
+    for (int t = r0 + wave; t < min(tend, r0 + round); t += 2 * W) {
+      tail(t, ra);
+      if (t + W < tend) tail(t + W, rb);
     }
-    if (r0 + round >= kend) break;
+    if (r0 + round >= tend) break;
     __syncthreads();
     const int most = most_candidates();
     if (most > CAP) break;
@@ -943,14 +943,14 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
     __syncthreads();
     RowLists<KO, 1> top;
     top.init(lists + wave * kWave, lists + (W + wave) * kWave);
-    for (int t0 = t_first; t0 < kend; t0 += W * kTile) {
+    for (int t = t_first; t < tend; t += W) {
       float v[R];
-      load(t0, ra);
-      score(t0, ra, v);
+      load(t, ra);
+      score(t, ra, v);
       float sv = v[0];
 #pragma unroll
       for (int x = 1; x < R; ++x) sv = x == r ? v[x] : sv;
-      top.offer(0, sv, t0 + lane);
+      top.offer(0, sv, t * kTile + lane);
     }
     top.finish(0);
     __syncthreads();
@@ -4781,8 +4781,8 @@ void launch_decode(const uint8_t* index, int nt, int B, int H_q, int H_kv, int g
     }
     want = std::min({want, (n + kDecodeMin - 1) / kDecodeMin, (size_t)p0.n_chunks});
   }
-  const int chunk = (int)saki::round_up((n + want - 1) / want, kTile);
-  const int n_chunks = (int)((n + chunk - 1) / chunk);
+  const int tiles = (int)saki::n_tiles((int)n), chunk = (int)((n + want * kTile - 1) / (want * kTile));  // in tiles
+  const int n_chunks = (tiles + chunk - 1) / chunk;
   uint64_t* part = n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p0.part_off) : nullptr;
   const long long groups = (long long)row_groups * n_chunks * n_bi;
   hipLaunchKernelGGL((score_decode_kernel<RK, ST, R>), dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)),

@@ -156,3 +156,42 @@ def test_decode_scores_that_are_no_numbers(sketch, H_q, shared):
         out += S.saki_score_topk(index, sketch, q, B_q, mu, 1, N, N, r, index_heads=1 if shared else H_q)
     assert (out[2] % 64 >= 32).all() and (out[3] > 0).all()
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+@pytest.fixture
+def largest_index():
+    """An fp8 index of 2^31 - 1 keys at rank 16 (34 GB): zero codes but for 40
+    keys along the sign of z, half of them at twice the length, some of them the
+    cache's last ones.  Returns (index, N, q, B_q, the expected list)."""
+    N, r = 2 ** 31 - 1, 16
+    if torch.cuda.mem_get_info()[0] < 48 << 30:
+        pytest.skip("needs 48 GB of GPU memory")
+    g = torch.Generator(device=DEV).manual_seed(6)
+    q = torch.randn((1, 1, 1, D), generator=g, device=DEV)
+    B_q = torch.randn((1, D, r), generator=g, device=DEV) / D ** 0.5
+    sign = torch.where(q[0, 0] @ B_q[0] < 0, 0x80, 0).to(torch.uint8)
+    at = torch.cat([torch.randint(2 ** 30, (20,), generator=g, device=DEV) * 2,
+                    N - 1 - torch.randperm(9000, generator=g, device=DEV)[:18],
+                    torch.tensor([0, N - 1], device=DEV)])
+    at = at[torch.randperm(40, generator=g, device=DEV)]
+    index = torch.zeros(S.saki_index_bytes(1, 1, N, r, "fp8"), dtype=torch.uint8, device=DEV)
+    code = index.view(-1, r)  # 16-byte codes in the order of the keys
+    code[at[:20]] = 0x40 + sign  # 2.0
+    code[at[20:]] = 0x38 + sign  # 1.0
+    zero = torch.arange(100, device=DEV)
+    zero = zero[~torch.isin(zero, at)][:24]
+    want = torch.cat([at[:20].sort().values, at[20:].sort().values, zero]).int()
+    yield index, N, q, B_q, want
+    del index, code
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("H_q", [1, 4])
+def test_decode_largest_cache(largest_index, H_q):
+    """Key numbers up to 2^31 - 2: the loops' steps past the last tile."""
+    index, N, q, B_q, want = largest_index
+    idx, sc = S.saki_score_topk(index, "fp8", q.expand(1, H_q, 1, D).contiguous(),
+                                B_q.expand(H_q, D, 16).contiguous(), torch.zeros((1, D), device=DEV), 1, N, N,
+                                16, index_heads=1)
+    assert torch.equal(idx[0, :, 0], want.expand(H_q, 64))
+    assert (sc[..., 40:] == 0).all() and (sc[..., :40] > 0).all()
