@@ -14,6 +14,7 @@ constexpr int kChunkBytes = 16;
 constexpr int kScanWaves = 1;          // waves per work-group of the one-pass MFMA scoring kernel
 constexpr int kScanMinKeys = 16384;    // rows at least this long take it
 constexpr int kBatchMaxChunk = 4096;   // keys per chunk of the two-pass MFMA scoring kernel
+constexpr size_t kMaxChunk = 0x7fff0000;  // keys per chunk of any kernel: steps past its end fit an int
 constexpr int kBatchWaves = 1;         // its waves per work-group (16 rows each)
 
 inline bool rank_supported(int r) { return r == 16 || r == 32 || r == 64 || r == 128; }
@@ -70,6 +71,7 @@ inline Plan make_plan(int B, int heads, int Q, int N_valid, int part_entry_bytes
     if (c < 2048) c = 2048;
     if (c < chunk) chunk = c;
   }
+  if (chunk > kMaxChunk) chunk = kMaxChunk;
   p.chunk = (int)chunk;
   p.n_chunks = (int)((n + chunk - 1) / chunk);
   const size_t rows_total = (size_t)B * H_q * Q;

@@ -2165,26 +2165,27 @@ __global__ __launch_bounds__(kScanWaves * kWave) void score_scan_kernel(
   // with `only`, the rows to redo (a wave with none has nothing to do)
   const bool want = row_ok && (!only || only[bh * Q + my_row] != 0);
   if (only && __ballot(want) == 0) return;
-  const int my_lim = row_limit(my_row, Q, N_valid, q_pos);
-  const int kmax = wave_max_i(my_lim);
-  const int kmin = wave_min_i(row_ok ? my_lim : INT_MAX);
+  // keys are counted from the chunk's first one: steps past the last of nearly
+  // 2^31 keys would not fit an int
   const int kbeg = ch * chunk;
-  const int kend = min(kbeg + chunk, kmax);
+  const int my_lim = min(row_limit(my_row, Q, N_valid, q_pos) - kbeg, chunk);
+  const int kend = wave_max_i(my_lim);
+  const int kmin = wave_min_i(row_ok ? my_lim : INT_MAX);
   K* list = list_mem[wave];
   K* buf = buf_mem[wave];
 
   const size_t code_set = (bh / H_q) * (H_q / gq) + h / gq;
-  const uint8_t* hbase = index + code_set * n_tiles * Scorer::TB;
+  const uint8_t* hbase = index + (code_set * n_tiles + kbeg / kTile) * Scorer::TB;
   // the gate's sample: every stride-th tile of the chunk, at most kScanSample;
   // the first kSA of them are requested before the query sketch is formed
-  const int n_row = row_ok ? max(0, min(my_lim, kend) - kbeg) : 0;
+  const int n_row = row_ok ? max(0, my_lim) : 0;
   const bool gated = !only && wave_max_i(n_row) >= kScanGateKeys;
-  const int stride = max(1, (kend - kbeg) / (kTile * kScanSample)) * kTile;
-  const int n_samp = gated ? min(kScanSample, (kend - kbeg + stride - 1) / stride) : 0;
+  const int stride = max(1, kend / (kTile * kScanSample)) * kTile;
+  const int n_samp = gated ? min(kScanSample, (kend - 1) / stride + 1) : 0;
   constexpr int kSA = Scorer::NL == 1 ? 4 : Scorer::kPrefetch ? 2 : 1;
   Scorer sc;
   typename Scorer::Raw sraw[kSA];
-  auto sample_at = [&](int i) { return hbase + (size_t)((kbeg + i * stride) / kTile) * Scorer::TB; };
+  auto sample_at = [&](int i) { return hbase + (size_t)(i * stride / kTile) * Scorer::TB; };
 #pragma unroll
   for (int u = 0; u < kSA; ++u)
     if (u < n_samp) sc.load(sample_at(u), qi, g, sraw[u]);
@@ -2207,7 +2208,7 @@ __global__ __launch_bounds__(kScanWaves * kWave) void score_scan_kernel(
         f32x4_t acc[4];
         sc.mma(sraw[u], acc);
         if (i + kSA < n_samp) sc.load(sample_at(i + kSA), qi, g, sraw[u]);
-        const int t0 = kbeg + i * stride;
+        const int t0 = i * stride;
 #pragma unroll
         for (int sub = 0; sub < 4; ++sub)
 #pragma unroll
@@ -2245,7 +2246,7 @@ __global__ __launch_bounds__(kScanWaves * kWave) void score_scan_kernel(
     wave_lds_sync();
   };
   auto scan = [&]() {
-    sc.for_tiles_deep(hbase, kbeg, kend, qi, g, [&](int t0, f32x4_t* acc) {
+    sc.for_tiles_deep(hbase, 0, kend, qi, g, [&](int t0, f32x4_t* acc) {
       uint32_t take = 0;
 #pragma unroll
       for (int sub = 0; sub < 4; ++sub)
@@ -2301,7 +2302,7 @@ __global__ __launch_bounds__(kScanWaves * kWave) void score_scan_kernel(
         for (int m = 0; m < 2; ++m) s2[m] = pick(m2, s4[2 * m + 1], s4[2 * m]);
         const float sv = __uint_as_float(pick(m3, s2[1], s2[0]));
         if (take) {
-          buf[qi * kScanBuf + pos] = KO::make(sv, t0 + 16 * (e >> 2) + 4 * g + (e & 3));
+          buf[qi * kScanBuf + pos] = KO::make(sv, kbeg + t0 + 16 * (e >> 2) + 4 * g + (e & 3));
           ++pos;
           take &= take - 1;
         }
@@ -4743,7 +4744,7 @@ saki::Plan one_round(saki::Plan p, K kernel, int groups_per_chunk, int chunks_pe
   const size_t n = N_valid > 0 ? (size_t)N_valid : 1;
   size_t chunk = saki::round_up((n + want - 1) / want, kTile);
   const int n_chunks = (int)((n + chunk - 1) / chunk);
-  if (n_chunks >= p.n_chunks) return p;
+  if (n_chunks >= p.n_chunks || chunk > saki::kMaxChunk) return p;
   p.chunk = (int)chunk;
   p.n_chunks = n_chunks;
   return p;

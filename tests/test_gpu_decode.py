@@ -186,12 +186,13 @@ def largest_index():
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("H_q", [1, 4])
-def test_decode_largest_cache(largest_index, H_q):
-    """Key numbers up to 2^31 - 2: the loops' steps past the last tile."""
+@pytest.mark.parametrize("H_q,Q", [(1, 1), (4, 1), (1, 17)])
+def test_largest_cache(largest_index, H_q, Q):
+    """Key numbers up to 2^31 - 2: the loops' steps past the last tile, in the
+    decode scorer (one and four rows a work-group) and the one-pass scan."""
     index, N, q, B_q, want = largest_index
-    idx, sc = S.saki_score_topk(index, "fp8", q.expand(1, H_q, 1, D).contiguous(),
+    idx, sc = S.saki_score_topk(index, "fp8", q.expand(1, H_q, Q, D).contiguous(),
                                 B_q.expand(H_q, D, 16).contiguous(), torch.zeros((1, D), device=DEV), 1, N, N,
                                 16, index_heads=1)
-    assert torch.equal(idx[0, :, 0], want.expand(H_q, 64))
+    assert torch.equal(idx[0], want.expand(H_q, Q, 64))
     assert (sc[..., 40:] == 0).all() and (sc[..., :40] > 0).all()
