@@ -4321,13 +4321,28 @@ __global__ __launch_bounds__(W * kWave) void attend_kernel(
 //     first).  As r FMAs a key and dim, 19,200 rows took 262 us at r = 32 and
 //     96,000 rows 10 ms at r = 128 with float32 codes.
 // The work-groups stay for the whole launch (one per CU, the table takes its
-// LDS), which pays from kAttendManyRows rows on, and with B_q staged per head
-// from kAttendHeadRows rows of a head.
+// LDS).  With B_q staged per head that pays from kAttendManyRows rows on.  Exact
+// keys also need kAttendExactRows of them, as the rows that share a KV head's
+// gathers, the table and its reach do.  Against attend_kernel, us, lists spread
+// evenly over N float32 keys:
+//   rows (H_q x Q, sequences)   N = 1,000      12,000      32,768       131,072
+//   2,048 (32 x 1, 64)           23 / 24      27 / 25      30 / 26       30 / 25
+//   8,192 (32 x 1, 256)          93 / 92     103 / 100    104 / 96
+//   2,048 (32 x 64, 1)           14 / 19      23 / 23      28 / 24       30 / 26
+//   3,584 (28 x 128, 1)          15 / 28      28 / 34      38 / 38       42 / 39
+//   8,192 (32 x 256, 1)          27 / 58      54 / 65      75 / 77       87 / 85
+//   129,024 (32 x 4,032, 1)     333 / 841    750 / 910  1,033 / 1,006  1,282 / 1,147
+// so one query a head (and up to 63) stays with attend_kernel, and so do keys
+// past kAttendFarKeys, or past the table's reach for fewer than kAttendFarRows
+// rows (bf16 keys gain more at 32,768: 16,384 causal rows of 32 heads 3,099 / 3,937).
 constexpr int kAttendRowWaves = 16;
 constexpr int kRotLo = 64;
 constexpr int kRotRows = 256;          // 128 KiB of LDS, fewer beside a large B_q
 constexpr int kAttendHeadRows = 64;
 constexpr int kAttendManyRows = 1536;
+constexpr int kAttendExactRows = 2048;
+constexpr int kAttendFarRows = 3584;
+constexpr int kAttendFarKeys = 32768;
 constexpr int kAttendRowsMaxCap = 1 << 22;  // a head's keys within 32-bit byte offsets
 
 // v of lane N of this lane's row of 16
@@ -4395,14 +4410,15 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
   const int r_end = (int)min((long long)n_rows, (lg + 1) * per_group);
   const int steps = (k + 15) / 16;
   const int my_e = 16 * (qi >> 2) + 4 * g + (qi & 3);  // this lane's list entry
-  // the rows of one head at a time (uniform over the work-group)
+  // with B_q staged, the rows of one head at a time (uniform over the work-group)
   for (int seg = (int)(lg * per_group), seg_end; seg < r_end; seg = seg_end) {
-  const int bh = seg / Q, h = bh % H_q;
-  seg_end = min(r_end, (bh + 1) * Q);
-  const size_t kv = (size_t)(bh / H_q) * H_kv + h / (H_q / H_kv);
-  const uint8_t* cb = index + ((size_t)(bh / H_q) * index_heads + h / (H_q / index_heads)) * n_tiles * TB;
+  const int seg_bh = seg / Q;
+  seg_end = RECON ? min(r_end, (seg_bh + 1) * Q) : r_end;
+  const uint8_t* cb = nullptr;
   float m0[4], m1[4];
   if constexpr (RECON) {
+    const int h = seg_bh % H_q, g_kv = h / (H_q / H_kv);
+    cb = index + ((size_t)(seg_bh / H_q) * index_heads + h / (H_q / index_heads)) * n_tiles * TB;
     __syncthreads();  // the previous head's reads are done
     for (int e = threadIdx.x; e < NK * 8 * kWave; e += kAttendRowWaves * kWave) {
       const int l = e % kWave, mb = e / kWave % 8, kk = e / kWave / 8;
@@ -4421,14 +4437,15 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
 #pragma unroll
       for (int p = 0; p < 3; ++p) bqs[kk][mb][p][l] = uint4{t[0][p], t[1][p], t[2][p], t[3][p]};
     }
-    const float4 x = *reinterpret_cast<const float4*>(mu + (kv % H_kv) * D + 4 * qi);
-    const float4 y = *reinterpret_cast<const float4*>(mu + (kv % H_kv) * D + HALF + 4 * qi);
+    const float4 x = *reinterpret_cast<const float4*>(mu + (size_t)g_kv * D + 4 * qi);
+    const float4 y = *reinterpret_cast<const float4*>(mu + (size_t)g_kv * D + HALF + 4 * qi);
     m0[0] = x.x; m0[1] = x.y; m0[2] = x.z; m0[3] = x.w;
     m1[0] = y.x; m1[1] = y.y; m1[2] = y.z; m1[3] = y.w;
     __syncthreads();
   }
   for (int row = seg + wave; row < seg_end; row += kAttendRowWaves) {
-    const int i = row - bh * Q;
+    const int bh = RECON ? seg_bh : row / Q, i = row - bh * Q;
+    const size_t kv = (size_t)(bh / H_q) * H_kv + bh % H_q / (H_q / H_kv);
     const char* kb = reinterpret_cast<const char*>(keys) + kv * N_cap * D * (KBF ? 2 : 4);
     const char* vb = reinterpret_cast<const char*>(values + kv * N_cap * D);
     int my_j = my_e < k ? top_idx[(size_t)row * k + my_e] : -1;
@@ -4663,8 +4680,10 @@ void launch_attend(const void* keys, const float* values, const uint8_t* index, 
                                 : reinterpret_cast<uintptr_t>(keys);
     const bool al = ((src | reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(q) |
                       reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    if (al && rows >= (size_t)kAttendManyRows && rows <= 0x7fffffffu && N_cap <= kAttendRowsMaxCap &&
-        (!RECON || Q >= kAttendHeadRows)) {
+    const size_t far_keys = rows >= (size_t)kAttendFarRows ? kAttendFarKeys : (kRotRows - kRotLo) * kRotLo;
+    const bool many = RECON ? rows >= (size_t)kAttendManyRows
+                            : rows >= (size_t)kAttendExactRows && (size_t)N_valid <= far_keys;
+    if (al && many && Q >= kAttendHeadRows && rows <= 0x7fffffffu && N_cap <= kAttendRowsMaxCap) {
       const int slots = resident_groups(attend_rows_kernel<RK, KBF, ST, RECON>, kAttendRowWaves * kWave);
       if (slots > 0) {
         const int per = std::max(kAttendRowWaves, (int)((rows + slots - 1) / slots));

@@ -186,10 +186,11 @@ def test_attend_sequences_groups_short_and_skipped_lists():
 @pytest.mark.parametrize("k,N,Q,far,keys_bf16", [(64, 1100, 1030, False, False), (10, 130, 1025, True, True),
                                                  (33, 64, 1030, True, False)])
 def test_attend_many_rows(k, N, Q, far, keys_bf16):
-    """4,096 rows and more take the kernel with the rotation table: lists of
-    every length up to its four steps, skipped entries, empty rows, and
-    positions whose distance to a key is negative or past the table.  Checked
-    on rows spread over the launch."""
+    """2,048 rows and more, 64 or more a head, take the kernel with the rotation
+    table: lists of every length up to its four steps, skipped entries, empty
+    rows, heads that begin inside a work-group's rows, and positions whose
+    distance to a key is negative or past the table.  Checked on rows spread
+    over the launch."""
     rng = np.random.default_rng(k)
     keys = rng.standard_normal((1, 2, N, 128)).astype(np.float32)
     if keys_bf16:
@@ -252,3 +253,37 @@ def test_attend_many_rows_reconstructed(sketch, r, shared):
         extra = np.stack([qn[i] * dk[idx[0, h, i]] / np.sqrt(128) for i in rows])
         assert np.all(out[0, h, 5] == 0.0)
         _check(out[0, h, rows], q[0, h, rows], pos[rows], khat, values[0, g], idx[0, h, rows], extra)
+
+
+@pytest.mark.parametrize("Q,batch,H_q,H_kv", [(1, 64, 32, 8), (1, 73, 28, 4), (4, 43, 12, 4), (63, 3, 12, 2)])
+def test_attend_many_rows_of_few_queries(Q, batch, H_q, H_kv):
+    """Batched decode: as many rows as the kernel with the rotation table takes,
+    but few of each head.  The rows of a wave (one at a time there) would keep
+    most of a work-group waiting; they must not take longer than half as many
+    rows twice, with a third more for the clock, and agree with the oracle."""
+    N, k = 900, 64
+    g = torch.Generator(device=DEV).manual_seed(Q)
+    values, keys = (torch.randn((batch, H_kv, N, 128), generator=g, device=DEV) for _ in range(2))
+    q = torch.randn((batch, H_q, Q, 128), generator=g, device=DEV)
+    idx = torch.argsort(torch.rand((batch, H_q, Q, N), generator=g, device=DEV), dim=-1)[..., :k].int().contiguous()
+    out = S.saki_attend(values, q, idx, N, keys=keys)
+    for b, h in {(0, 0), (batch - 1, H_q - 1), (batch // 2, H_q // 2)}:
+        rows = np.unique([0, Q // 2, Q - 1])
+        _check(out[b, h].cpu().numpy()[rows], q[b, h].cpu().numpy()[rows], np.full(len(rows), N - 1),
+               keys[b, h // (H_q // H_kv)].cpu().numpy(), values[b, h // (H_q // H_kv)].cpu().numpy(),
+               idx[b, h].cpu().numpy()[rows])
+
+    def us(n):
+        args = values[:n], q[:n], idx[:n], N
+        best = float("inf")
+        for _ in range(6):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(20):
+                S.saki_attend(*args, keys=keys[:n], out=out[:n])
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 50)
+        return best
+
+    assert us(batch) <= 4 / 3 * 2 * us((batch + 1) // 2)
