@@ -4312,7 +4312,9 @@ __global__ __launch_bounds__(W * kWave) void attend_kernel(
 //     For 0 <= pos - j < 64 n_hi, t = t_hi + t_lo with the sines and cosines of
 //     both in LDS (64 low and n_hi high rows, float32 values rounded from
 //     float64): an angle sum costs four operations.  A step with another
-//     difference evaluates its angles (reduced in float64).
+//     difference evaluates its angles (reduced in float64) from the pairs' turns
+//     in LDS: formed anew, four exp a lane, they made reconstruction from bf16
+//     codes over 131,072 keys (129,024 rows, r = 32) 1,524 us instead of 1,172.
 //   - Reconstructed keys are a contraction, mu + B_q c: the codes of 16 listed
 //     keys (rows) times the head's B_q (columns, in the order of the dims above,
 //     so that a lane receives just its own) on the bf16 MFMA.  B_q waits in LDS
@@ -4375,7 +4377,7 @@ template <int RK>
 constexpr int attend_bq_bytes() { return (RK + 31) / 32 * 8 * 3 * kWave * 16; }
 template <bool RECON, int RK>
 constexpr int attend_rot_rows() {
-  return RECON ? std::min(kRotRows, (160 * 1024 - attend_bq_bytes<RK>()) / 512) : kRotRows;
+  return RECON ? std::min(kRotRows, (160 * 1024 - attend_bq_bytes<RK>()) / 512 - 1) : kRotRows;
 }
 template <int RK, bool KBF, int ST, bool RECON>
 __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
@@ -4392,11 +4394,13 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
   __shared__ __align__(16) float rot[attend_rot_rows<RECON, RK>()][D];  // cosines of pairs 0 .. 63, then sines
   // term p of B_q[dim(mb, qi)][32 kk + 8 g .. + 7], dim(mb, qi) = 64 (mb / 4) + 4 qi + mb % 4
   __shared__ uint4 bqs[RECON ? NK : 1][RECON ? 8 : 1][RECON ? 3 : 1][RECON ? kWave : 1];
+  __shared__ __align__(16) double turns[HALF];  // quarter turns per position of the pairs
   const long long lg = xcd_logical_block(groups);
   if (lg < 0) return;  // uniform over the work-group
   {
     const int l = threadIdx.x % HALF;
     const double turn = rope_quarter_turns(l, log_theta);
+    if (threadIdx.x < HALF) turns[l] = turn;
     for (int e = threadIdx.x / HALF; e < kRotLo + n_hi; e += kAttendRowWaves * kWave / HALF) {
       float sn, cs;
       rope_sincos_quarters<double>((e < kRotLo ? e : (e - kRotLo) * kRotLo) * turn, &sn, &cs);
@@ -4489,7 +4493,7 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
       } else {
         double turn[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) turn[e] = rope_quarter_turns(4 * qi + e, log_theta);
+        for (int e = 0; e < 4; ++e) turn[e] = turns[4 * qi + e];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const double dp = (double)pos - (double)jv[v];

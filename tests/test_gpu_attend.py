@@ -287,3 +287,38 @@ def test_attend_many_rows_of_few_queries(Q, batch, H_q, H_kv):
         return best
 
     assert us(batch) <= 4 / 3 * 2 * us((batch + 1) // 2)
+
+
+@pytest.mark.parametrize("r,reach", [(None, 12288), (128, 4032), (32, 12288)])
+def test_attend_at_the_reach_of_the_rotation_table(r, reach):
+    """Distances on both sides of the last one the table holds (its high rows
+    make way for B_q and the pairs' turns), alone and in one list."""
+    N, H, Q, k = reach + 100, 32 if r else 56, 64, 48
+    g = torch.Generator(device=DEV).manual_seed(N)
+    keys, values = (torch.randn((1, 1, N, 128), generator=g, device=DEV) for _ in range(2))
+    q = torch.randn((1, H, Q, 128), generator=g, device=DEV)
+    pos = torch.full((Q,), N - 1, dtype=torch.int32, device=DEV)
+    pos[1::2] = reach + torch.arange(Q // 2, dtype=torch.int32, device=DEV)
+    j = torch.randint(0, 40, (1, H, Q, k), generator=g, device=DEV)
+    j[..., ::3] += N - reach - 60  # around the reach from position N - 1
+    j[..., 1::3] += 200
+    if r is None:
+        out = S.saki_attend(values, q, j.int().contiguous(), N, keys=keys, q_pos=pos)
+        khat, extra = keys[0, 0].double().cpu().numpy(), None
+    else:
+        B_k, B_q = (torch.randn((H, 128, r), generator=g, device=DEV) / 11 for _ in range(2))
+        mu = torch.randn((1, 128), generator=g, device=DEV)
+        index = S.saki_build_index(keys, B_k, mu, r, "f32", H)
+        out = S.saki_attend(values, q, j.int().contiguous(), N, index=index, sketch="f32", B_q=B_q, mu=mu, r=r,
+                            q_pos=pos)
+        codes = S.saki_index_export(index, "f32", 1, H, N, r)[0].double().cpu().numpy()
+    rows = np.array([0, 1, 2, 17, Q - 1])
+    for h in (0, 13, H - 1):
+        qh, jh = q[0, h].cpu().numpy()[rows], j[0, h].cpu().numpy()[rows].astype(np.int32)
+        if r is not None:
+            w, m = B_q[h].double().cpu().numpy(), mu[0].double().cpu().numpy()
+            khat = m + codes[h] @ w.T
+            # float32 sums: r products, 2^-24 each, of the absolute sums
+            dk = np.linalg.norm((np.abs(codes[h]) @ np.abs(w).T + np.abs(m)) * r * 2.0 ** -24, axis=1)
+            extra = np.linalg.norm(qh, axis=1)[:, None] * dk[jh] / np.sqrt(128)
+        _check(out[0, h].cpu().numpy()[rows], qh, pos.cpu().numpy()[rows], khat, values[0, 0].cpu().numpy(), jh, extra)
