@@ -1777,8 +1777,13 @@ __global__ __launch_bounds__(kBWaves * kWave) void score_batch_kernel(
   bmin = fminf(bmin, xor_shfl_f32(bmin, 16));
   bmin = fminf(bmin, xor_shfl_f32(bmin, 32));
   const int n_ent = row_tiles * 4 * lane_ent;
-  float tau = -FLT_MAX;  // rows with fewer than 64 blocks keep every key
-  bool done = bcnt < (float)kList;
+  // rows with fewer than 64 blocks keep every key, and so do rows of up to two
+  // tiles, whose keys (32 a lane) have room: of 64 of them a threshold from
+  // rounded scores may leave out one, and the fallback takes the wave (16
+  // queries over 64 float32 keys of r = 32, 32 heads: 31 us, now 13)
+  float tau = -FLT_MAX;
+  static_assert(2 * kTile / 4 < kBSlots, "two tiles of candidates fit a lane");
+  bool done = bcnt < (float)kList || row_tiles <= 2;
   float lo = 0.f, hi = 0.f;
   if (!done) {
     const float mean = bsum / bcnt;

@@ -89,3 +89,49 @@ def test_two_chunks_ragged_tiles_and_small_k():
     for k in (64, 10):
         out = gpu_pipeline(inp, 32, "bf16", k=k)
         _check_all_heads(inp, out, 32, "bf16_emul", k=k)
+
+
+@pytest.mark.parametrize("N", [63, 64, 65, 70, 128, 129])
+@pytest.mark.parametrize("sketch,r", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 32)])
+def test_rows_of_up_to_two_tiles(N, sketch, r):
+    """Rows that keep every key, one key more than that, and causal rows of both
+    kinds, against float64 scores of the exported codes."""
+    from tests.test_gpu_decode import _check
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    keys = torch.randn((1, 2, N, 128), generator=g, device="cuda:0")
+    q = torch.randn((1, 4, 19, 128), generator=g, device="cuda:0")
+    _check(keys, q, r, sketch)
+    pos = torch.arange(N - 18, N + 1, dtype=torch.int32, device="cuda:0")
+    _check(keys, q, r, sketch, q_pos=pos)
+
+
+def test_rows_of_64_keys_are_not_selected_online():
+    """A threshold from rounded scores left out one of 64 keys and sent every
+    wave to the online selection, twice the time of rows of 62 keys."""
+    g = torch.Generator(device="cuda:0").manual_seed(0)
+    r, Q = 32, 16
+    B_k, B_q = (torch.randn((32, 128, r), generator=g, device="cuda:0") / 11 for _ in range(2))
+    mu = torch.zeros((8, 128), device="cuda:0")
+    q = torch.randn((1, 32, Q, 128), generator=g, device="cuda:0")
+
+    def us(N):
+        keys = torch.randn((1, 8, N, 128), generator=g, device="cuda:0")
+        index = S.saki_build_index(keys, B_k, mu, r, "f32", 32)
+        ws = torch.empty(S.saki_score_topk_workspace_bytes(1, 32, Q, N, r, 64, "f32"), dtype=torch.uint8,
+                         device="cuda:0")
+        out = S.saki_score_topk(index, "f32", q, B_q, mu, 8, N, N, r, ws=ws)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                S.saki_score_topk(index, "f32", q, B_q, mu, 8, N, N, r, ws=ws, top_idx=out[0], top_score=out[1])
+        best = float("inf")
+        for _ in range(6):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            graph.replay()
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 50)
+        return best
+
+    assert us(64) <= 1.5 * us(62)
