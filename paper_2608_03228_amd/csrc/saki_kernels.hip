@@ -571,9 +571,10 @@ __device__ __forceinline__ bf16x2_t as_bf16x2(uint32_t v) {
 // Few query rows per code set.  The rows of a code set are its gq = H_q /
 // index_heads query heads times the Q queries, numbered rho = i * gq + (h % gq),
 // so that a work-group's R rows are the heads sharing the codes (for a
-// GQA-shared index) before further queries.  A work-group of W = 8 or 16 waves
+// GQA-shared index) before further queries.  A work-group of W = 4, 8 or 16 waves
 // takes R rows and one chunk of keys, wave w the tiles w, w + W, ... of it, one
-// key of a tile per lane, and leaves one sorted top-64 per row.
+// key of a tile per lane, and leaves one sorted top-64 per row (W = 4 too for
+// one row of a few keys; launch_decode has the rule).
 //   sketch  z = B_q^T q (rounded to bf16 for bf16 and fp8 codes) and b = q^T mu
 //           (Sec. 6), float32 sums of 128 / W dims per wave, added in wave
 //           order; the wave's first tiles are requested before.
@@ -597,6 +598,12 @@ constexpr int kDecodeTiles = 8;   // head tiles per wave
 constexpr int kDecodeRound = 16;  // tail tiles per wave between checks
 template <int R>
 constexpr int decode_cap() { return R >= 4 ? 512 : 1024; }
+// Bytes of LDS that W waves share besides the kernel's own arrays.
+template <int RK, int R>
+constexpr size_t decode_area(int W) {
+  const size_t part = (size_t)W * R * (RK + 1) * 4, most = (size_t)R * W * kWave * 4, lists = (size_t)W * kWave * 16;
+  return std::max(part, std::max(most, lists));
+}
 
 // Merges the n sorted lists of 64 at m[(r * stride + i) * 64], i < n, of each
 // row r < R into list 0 of the row, by all waves of the work-group.
@@ -634,9 +641,7 @@ __global__ __launch_bounds__(kDecodeWaves * kWave) void score_decode_kernel(
   constexpr int D = saki::kHeadDim;
   constexpr int WM = kDecodeWaves, T = kDecodeTiles, CAP = decode_cap<R>();
   constexpr int NO = R * (RK + 1);  // sketch outputs of R rows
-  constexpr size_t kPartB = (size_t)WM * NO * 4, kMaxB = (size_t)R * WM * kWave * 4, kRowB = (size_t)WM * kWave * 16;
-  constexpr size_t kArea = kPartB > kMaxB ? (kPartB > kRowB ? kPartB : kRowB) : (kMaxB > kRowB ? kMaxB : kRowB);
-  __shared__ __align__(16) uint8_t area[kArea];  // sketch parts, lane maxima, online lists
+  extern __shared__ __align__(16) uint8_t area[];  // decode_area<RK, R>(W): sketch parts, lane maxima, online lists
   __shared__ float zs[R][RK + 1];                // element RK: the mean term b
   __shared__ __align__(16) uint32_t zw[R][RK / 2];  // pairs of bf16 elements
   __shared__ K buf[R][CAP];
@@ -4654,7 +4659,7 @@ __global__ __launch_bounds__(kAttendRowWaves * kWave) void attend_rows_kernel(
 // device at once, or 0 if the runtime cannot tell.  Cached per (kernel,
 // block size, device).
 template <class K>
-int resident_groups(K kernel, int threads) {
+int resident_groups(K kernel, int threads, size_t lds = 0) {
   static std::mutex mu;
   static std::map<std::tuple<const void*, int, int>, int> cache;
   int dev = 0;
@@ -4667,7 +4672,7 @@ int resident_groups(K kernel, int threads) {
   }
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) {
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess) {
     (void)hipGetLastError();
     return 0;
   }
@@ -4778,34 +4783,55 @@ saki::Plan one_round(saki::Plan p, K kernel, int groups_per_chunk, int chunks_pe
   return p;
 }
 
-// Rows of up to kDecodeOne keys are one chunk (16 tiles a wave take about as
-// long as the merge launch that two chunks would need).  Longer ones are cut so
-// that the work-groups fill the GPU once, at least kDecodeMin keys each, in no
-// more chunks than the plan (which sized the workspace) has.  Work-groups have
-// 16 waves (fewer lists: 4 rows of each of 32 fp8 code sets over 100,003 keys
-// 43 us, with 8 waves 49), or 8 where 16 would leave chunks of more than
-// kDecodeLong keys (streaming counts then, and the waits of several small
-// work-groups at their barriers overlap: 32 rows over 2^20 keys 360 us, with
-// 16 waves 376).
+// Rows of up to kDecodeOne keys (half as many where a work-group has several
+// rows) and kDecodeOneBytes of codes are one chunk: so many take about as long
+// as the merge launch that two chunks would need (28 x 2 rows, bf16, r = 32:
+// 8,192 keys 17.8 us, 16,384 as one chunk 25.5, cut 19.7; 32 rows, float32, r =
+// 128: 8,192 keys 52 and 36).  Longer ones are cut so that the work-groups fill the GPU once, at least
+// kDecodeMin keys each, in no more chunks than the plan (which sized the
+// workspace) has.  Waves of a work-group (bf16 codes, r = 32):
+//   up to one work-group per CU: 16 (fewer lists: 4 rows of each of 32 fp8 code
+//     sets over 100,003 keys 43 us, with 8 waves 49), but 8 for short rows,
+//     whose waves mostly wait for each other (32 rows over 1,024 keys 9.1 us,
+//     with 16 waves 9.8; over 8,192 keys 13.2 and 13.1), and 4 for one row of
+//     up to four tiles (64 keys 5.5 us, with 8 waves 5.7, with 16 6.9);
+//   more work-groups than CUs: 8, as several small ones overlap their waits (4
+//     rows of 512 code sets over 64 keys 13 us, with 16 waves 23; over 4,096
+//     keys 38 and 50), and 4 for one row of up to kDecodeShort keys (two rows of
+//     each of 1,792 code sets over 64 keys, a work-group each, 17 us, with 8
+//     waves 28);
+//   chunks of more than kDecodeLong keys: 8 (streaming counts then: 32 rows
+//     over 2^20 keys 360 us, with 16 waves 376).
 constexpr int kDecodeOne = 16384;
 constexpr int kDecodeMin = 4096;
 constexpr int kDecodeLong = 32768;
+constexpr int kDecodeShort = 4096;              // keys
+constexpr size_t kDecodeShortBytes = 256 << 10;  // of codes
+constexpr size_t kDecodeOneBytes = 1 << 20;
+constexpr int kDecodeCus = 256;
+constexpr int kDecodeFew = 1024;
 template <int RK, int ST, int R>
 void launch_decode(const uint8_t* index, int nt, int B, int H_q, int H_kv, int gq, int N_valid,
                    const float* q, const int* q_pos, int Q, const float* Bq, const float* mu, int k,
                    int* top_idx, float* top_score, uint8_t* ws, const saki::Plan& p0, hipStream_t s) {
   const int n_bi = B * (H_q / gq), row_groups = (gq * Q + R - 1) / R;
   const size_t rows = (size_t)B * H_q * Q, n = N_valid > 0 ? (size_t)N_valid : 1;
-  int threads = kDecodeWaves * kWave;
+  const size_t bytes = n * RK * code_bytes<ST>();
+  int waves = kDecodeWaves;
+  if ((long long)row_groups * n_bi > kDecodeCus)
+    waves = R == 1 && n <= (size_t)kDecodeShort ? 4 : 8;
+  else if (n <= (size_t)kDecodeShort && bytes <= kDecodeShortBytes)
+    waves = R == 1 && n <= 4 * (size_t)kTile ? 4 : 8;
   size_t want = 1;
-  if (n > (size_t)kDecodeOne) {
+  if (n > (size_t)(R == 1 ? kDecodeOne : kDecodeOne / 2) || bytes > kDecodeOneBytes) {
     auto chunks = [&] {
-      const long long slots = resident_groups(score_decode_kernel<RK, ST, R>, threads);
+      const long long slots =
+          resident_groups(score_decode_kernel<RK, ST, R>, waves * kWave, decode_area<RK, R>(waves));
       return (size_t)std::max(1LL, slots / ((long long)row_groups * n_bi));
     };
     want = chunks();
-    if (n / want > (size_t)kDecodeLong) {
-      threads /= 2;
+    if (n / want > (size_t)kDecodeLong && waves > 8) {
+      waves = 8;
       want = chunks();
     }
     want = std::min({want, (n + kDecodeMin - 1) / kDecodeMin, (size_t)p0.n_chunks});
@@ -4814,8 +4840,9 @@ void launch_decode(const uint8_t* index, int nt, int B, int H_q, int H_kv, int g
   const int n_chunks = (tiles + chunk - 1) / chunk;
   uint64_t* part = n_chunks > 1 ? reinterpret_cast<uint64_t*>(ws + p0.part_off) : nullptr;
   const long long groups = (long long)row_groups * n_chunks * n_bi;
+  const size_t lds = decode_area<RK, R>(waves);
   hipLaunchKernelGGL((score_decode_kernel<RK, ST, R>), dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)),
-                     dim3(threads), 0, s, index, nt, N_valid, Q, q_pos, q, Bq, mu, H_q, H_kv,
+                     dim3(waves * kWave), lds, s, index, nt, N_valid, Q, q_pos, q, Bq, mu, H_q, H_kv,
                      gq, n_bi, row_groups, chunk, n_chunks, k, top_idx, top_score, part);
   if (n_chunks > 1)
     hipLaunchKernelGGL((merge_kernel<KeysF32, false>), dim3((unsigned)rows),
@@ -4867,8 +4894,11 @@ void launch_score(const uint8_t* index, int B, int H_q, int H_kv, int index_head
   const size_t rows = (size_t)B * H_q * Q;
   const int nt = (int)saki::n_tiles(N_cap);
   if (!p.mfma) {
+    // two and three rows over few keys are better work-groups of their own (two
+    // rows of each of 28 bf16 code sets over 512 keys 7.3 us, together 9.9; over
+    // 1,024 keys 8.9 and 12.8)
     const int n_rho = gq * Q;
-    if (n_rho == 1)
+    if (n_rho == 1 || (n_rho <= 3 && N_valid <= kDecodeFew))
       launch_decode<RK, ST, 1>(index, nt, B, H_q, H_kv, gq, N_valid, q, q_pos, Q, Bq, mu, k, top_idx, top_score, ws, p0, s);
     else if (n_rho == 2)
       launch_decode<RK, ST, 2>(index, nt, B, H_q, H_kv, gq, N_valid, q, q_pos, Q, Bq, mu, k, top_idx, top_score, ws, p0, s);

@@ -74,6 +74,49 @@ def test_decode_lists(N, Q, H_q, H_kv, shared, r, sketch):
     _check(keys, q, r, sketch, shared=shared)
 
 
+# the sizes at which a launch takes more waves, or cuts the keys, with as many
+# work-groups as CUs or fewer, and with one more
+@pytest.mark.parametrize("N,Q,H_q,H_kv,shared,r,sketch", [
+    (256, 1, 3, 1, False, 32, "bf16"), (257, 1, 3, 1, False, 64, "f32"), (1024, 3, 2, 1, False, 32, "fp8"),
+    (1025, 3, 2, 1, False, 32, "fp8"), (1024, 2, 2, 1, False, 128, "f32"), (2049, 2, 2, 2, True, 128, "f32"),
+    (4096, 1, 4, 1, True, 32, "bf16"), (4097, 1, 4, 1, True, 32, "bf16"), (8192, 1, 4, 1, True, 16, "bf16"),
+    (8193, 1, 4, 1, True, 16, "bf16"), (16384, 1, 1, 1, False, 32, "bf16"), (4100, 1, 2, 1, False, 128, "f32"),
+    (70, 1, 257, 1, False, 16, "fp8"), (1030, 1, 257, 1, False, 16, "bf16"), (4097, 1, 257, 1, False, 16, "fp8"),
+    (300, 2, 130, 1, False, 16, "f32"), (1100, 2, 257, 1, False, 16, "bf16"), (200, 5, 130, 1, False, 32, "bf16")])
+def test_decode_launch_rules(N, Q, H_q, H_kv, shared, r, sketch):
+    g = torch.Generator(device=DEV).manual_seed(N)
+    keys = torch.randn((1, H_kv, N, D), generator=g, device=DEV)
+    q = torch.randn((1, H_q, Q, D), generator=g, device=DEV)
+    _check(keys, q, r, sketch, shared=shared)
+
+
+def test_decode_of_many_short_caches():
+    """64 sequences of 32 code sets over 64 keys: as work-groups of 16 waves, 15
+    of them without a key, a step took 44 us, as work-groups of four 12."""
+    batch = 64
+    g = torch.Generator(device=DEV).manual_seed(batch)
+    B_k, B_q = (torch.randn((32, D, 32), generator=g, device=DEV) / 11 for _ in range(2))
+    mu = torch.zeros((8, D), device=DEV)
+    q = torch.randn((batch, 32, 1, D), generator=g, device=DEV)
+    keys = torch.randn((batch, 8, 64, D), generator=g, device=DEV)
+    index = S.saki_build_index(keys, B_k, mu, 32, "bf16", 32)
+    out = S.saki_score_topk(index, "bf16", q, B_q, mu, 8, 64, 64, 32)
+    graph = torch.cuda.CUDAGraph()
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            S.saki_score_topk(index, "bf16", q, B_q, mu, 8, 64, 64, 32, ws=ws, top_idx=out[0], top_score=out[1])
+    best = float("inf")
+    for _ in range(6):
+        t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        t0.record()
+        graph.replay()
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1) * 50)
+    assert best <= 24
+
+
 def test_decode_causal_and_short_k():
     """Rows with no key, fewer than k, limits on tile and head edges."""
     g = torch.Generator(device=DEV).manual_seed(1)
