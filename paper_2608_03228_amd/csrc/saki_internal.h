@@ -165,17 +165,45 @@ struct OncePlan {
 constexpr int kOnceMinChunk = 128;  // keys a wave takes at least
 constexpr int kOnceWaves = 4096;    // waves wanted over the whole GPU
 constexpr int kOnceMaxRows = 2048;  // rows of 16 or more queries a head that take it
+// Whether it is the better path.  Its decision rescores every listed key (25 to
+// 45 us per 1,000 rows), so it gains with the key reads that it saves.  us,
+// float32 keys, d = 128, this path / the other one; H_q / H_kv x Q, sequences:
+//   Q < 16, against one wave per 1 or 4 rows, which takes 0.2 us a key
+//     32 / 8 x 1, 1           64 keys 29 / 20    128 keys 33 / 33    300 keys 31 / 71
+//     32 / 8 x 2, 16                  46 / 24            55 / 42     256 keys 55 / 76
+//     32 / 8 x 2, 64                 120 / 102          139 / 196            144 / 386
+//     32 / 8 x 4, 1                   29 / 40            33 / 58              32 / 92
+//     32 / 8 x 4, 64                 222 / 135          254 / 200            235 / 321
+//     32 / 8 x 15, 4                  66 / 43            77 / 64              75 / 104
+//     32 / 8 x 15, 16                206 / 58           234 / 94             216 / 159
+//   Q >= 16, against 16 rows a wave    4,096 keys      8,192 keys      16,384 keys
+//     32 / 8 x 16, 4 (64 rows a group)   87 / 126                       138 / 394
+//     32 / 8 x 64, 1 (256)               96 / 99                        131 / 216
+//     28 / 4 x 73, 1 (511)              114 / 109       111 / 140       134 / 242
+//     8 / 1 x 64, 1 (512)                89 / 91         77 / 95         74 / 95
+//     2 / 1 x 400, 1 (800)              111 / 92        102 / 93         98 / 112
+//     1 / 1 x 2,000, 1 (2,000)          163 / 95        157 / 118       147 / 185
+//   More rows also gain from 16,384 keys on (28 / 4 x 128: 208 / 308), which
+//   kOnceMaxRows leaves to the other path.
+inline bool once_better(int H_q, int H_kv, int Q, size_t rows, int N_valid) {
+  const size_t group = (size_t)(H_q / H_kv) * Q;
+  size_t least;  // keys
+  if (Q < 4)
+    least = rows <= 1536 ? 129 : 32 * (size_t)Q + 1;
+  else if (Q < 16)
+    least = rows <= (Q < 8 ? 1024u : 512u) ? 0 : Q < 8 || rows <= 2048 ? 129 : Q < 12 ? 257 : 353;
+  else
+    least = group <= 384 || rows <= 512 ? 0 : group <= 512 ? 8192 : 16384;
+  return (size_t)N_valid >= least;
+}
 inline OncePlan recall_once_plan(int B, int H_q, int H_kv, int Q, int N_valid) {
   OncePlan o;
   if (Q <= 0 || N_valid <= 0) return o;  // no rows, or none with a key
   const Plan p = recall_plan(B, H_q, H_kv, Q, N_valid);
-  // The decision rescores every listed key (0.1 us a row) where the other path
-  // rescores a few: 16 queries over 4,096 keys (512 rows) 59 us against 97,
-  // over 262,144 keys 297 against 1,542; 17,536 rows over 4,096 keys 1,404
-  // against 406.
-  if (p.mfma && (p.n_chunks == 1 || (size_t)B * H_q * Q > (size_t)kOnceMaxRows)) return o;
-  o.stream = make_plan(B, H_q, Q, N_valid, 16, false);
   const size_t group_rows = (size_t)(H_q / H_kv) * Q, rows = (size_t)B * H_q * Q;
+  if (p.mfma && (p.n_chunks == 1 || rows > (size_t)kOnceMaxRows)) return o;
+  if (!once_better(H_q, H_kv, Q, rows, N_valid)) return o;
+  o.stream = make_plan(B, H_q, Q, N_valid, 16, false);
   o.nb = group_rows > 16 ? 2 : 1;
   o.row_blocks = (int)((group_rows + 16 * o.nb - 1) / (16 * o.nb));
   const size_t per_chunk = (size_t)o.row_blocks * B * H_kv, entry = 1024 + sizeof(int);

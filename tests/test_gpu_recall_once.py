@@ -127,3 +127,34 @@ def test_recall_once_small_workspace():
     keys, q = _inputs(13, 1, 2, 1, 1500, 2, False)
     want = _exact(keys, q, 1500, 64, None)
     _check(keys, q, 1500, 64, want, ws=torch.empty(1, dtype=torch.uint8, device=DEV))
+
+
+# both sides of the rule that chooses the path: keys for a few rows of a head,
+# for many rows, and rows of a KV group
+@pytest.mark.parametrize("B,H_q,H_kv,N,Q,k", [
+    (1, 4, 1, 128, 1, 64), (1, 4, 2, 129, 3, 64), (1, 4, 1, 20, 4, 64), (52, 30, 2, 32, 1, 64),
+    (52, 30, 2, 33, 1, 64), (26, 30, 6, 65, 2, 20), (8, 33, 3, 128, 4, 64), (8, 33, 3, 129, 4, 64),
+    (8, 28, 4, 256, 11, 64), (8, 28, 4, 257, 11, 64), (8, 28, 4, 352, 15, 64), (8, 28, 4, 353, 15, 64), (1, 16, 1, 4100, 40, 64), (1, 8, 1, 4100, 64, 64),
+    (1, 17, 1, 8192, 31, 64)])
+def test_recall_path_rule(B, H_q, H_kv, N, Q, k):
+    keys, q = _inputs(N + Q, B, H_q, H_kv, N, Q, False)
+    _check(keys, q, N, k, _near(_exact(keys, q, N, k, None), N, N))
+
+
+def test_recall_of_many_rows_over_few_keys():
+    """30,720 rows over 64 keys: decided row by row from scanned lists 760 us, one
+    wave per four rows 204."""
+    B, H, Q, N = 64, 32, 15, 64
+    g = torch.Generator(device=DEV).manual_seed(0)
+    keys, q = (torch.randn((B, h, n, D), generator=g, device=DEV) for h, n in ((8, N), (H, Q)))
+    lists = torch.argsort(torch.rand((B, H, Q, N), generator=g, device=DEV), dim=-1).int().contiguous()
+    ws = torch.empty(max(1, S.saki_recall_workspace_bytes(B, H, 8, Q, N, D, 64)), dtype=torch.uint8, device=DEV)
+    best = float("inf")
+    for _ in range(6):
+        t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        t0.record()
+        hits, _ = S.saki_recall(keys, q, lists, N, ws=ws)
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1) * 1e3)
+    assert (hits == 64).all() and best <= 400
