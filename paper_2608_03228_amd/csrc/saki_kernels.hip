@@ -4988,7 +4988,9 @@ void launch_recall(const void* keys, const float* q, const int* q_pos, int B, in
                    int* hits, int* exact_idx, uint8_t* ws, size_t ws_bytes, const saki::Plan& p,
                    hipStream_t s) {
   const saki::OncePlan op = saki::recall_once_plan(B, H_q, H_kv, Q, N_valid);
-  if (op.use && ws && ws_bytes >= op.ws_bytes) {
+  // its loads of keys and queries are 16 bytes wide, the other path's elements
+  const bool aligned = ((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(q)) & 15) == 0;
+  if (op.use && aligned && ws && ws_bytes >= op.ws_bytes) {
     if (op.nb == 2)
       launch_recall_once<KBF, 2>(keys, q, q_pos, B, H_q, H_kv, N_cap, N_valid, Q, k, approx, hits,
                                  exact_idx, ws, op, s);

@@ -158,3 +158,22 @@ def test_recall_of_many_rows_over_few_keys():
         t1.synchronize()
         best = min(best, t0.elapsed_time(t1) * 1e3)
     assert (hits == 64).all() and best <= 400
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("which", ["keys", "q"])
+def test_recall_of_unaligned_tensors(which, bf16):
+    """Keys and queries that begin one element past a 16-byte boundary."""
+    N, Q = 1300, 3
+    keys, q = _inputs(15, 1, 4, 2, N, Q, bf16)
+    want = _exact(keys, q, N, 64, None)
+
+    def odd(t):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)[1:]
+        flat.copy_(t.to(DEV).view(-1))
+        return flat.view(t.shape)
+
+    args = (odd(keys), q.to(DEV)) if which == "keys" else (keys.to(DEV), odd(q))
+    hits, ex = S.saki_recall(*args, torch.from_numpy(want).to(DEV), N)
+    assert args[which == "q"].data_ptr() % 16 != 0 and (hits == 64).all()
+    np.testing.assert_array_equal(ex.cpu().numpy(), want)
