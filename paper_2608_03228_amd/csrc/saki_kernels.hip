@@ -3104,10 +3104,17 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
       const uint32_t nxt = (uint32_t)__shfl_down((int)key, 1, kWave);
       const bool dup = lane < kWave - 1 && key == nxt;
       sl[r * kWave + lane] = key;
+      // every visible key is in T if its score is a number (finite operands;
+      // kbeg = 0, one chunk: the norms of the first tile)
+      bool odd = true;
       if (!ordered && lim_r <= k) {
-        // every visible key is in T: the list's distinct visible keys count,
-        // and the row is done (gate +inf).  As a row without a gate, each of
-        // them would be rescored and ranked.
+        const float* qr = q + (bh * Q + row0 + r) * saki::kHeadDim;
+        odd = !isfinite(qr[lane]) || !isfinite(qr[kWave + lane]) || (lane < lim_r && !isfinite(kn[lane]));
+      }
+      if (__ballot(odd) == 0) {
+        // the list's distinct visible keys count, and the row is done (gate
+        // +inf).  As a row without a gate, each of them would be rescored and
+        // ranked.
         const int n = __popcll(__ballot(key < (uint32_t)lim_r && !dup));
         if (lane == 0) {
           hits[bh * Q + row0 + r] = n;

@@ -68,3 +68,24 @@ def test_rows_hits_bad_lists():
     bad[0, 3, 0] = 10 ** 6
     bad[0, 4, :64] = -7
     _check(keys, q, pos, 900, 64, bad)
+
+
+def test_rows_hits_non_finite():
+    """Keys with infinite and NaN entries and queries of both kinds: scores that
+    are no numbers, or -inf, are not counted where the exact set leaves them out,
+    also of rows of at most k keys whose list names them."""
+    g = torch.Generator(device=DEV).manual_seed(8)
+    N, Q = 700, 1040
+    keys, q, pos = _case(1, 32, 8, N, Q, 0, False, 6)
+    keys[0, 0, 3, 5] = float("nan")
+    keys[0, 0, 7] = float("inf")
+    keys[0, 1, 9, 2] = -float("inf")
+    q[0, 9, 30, 1] = float("nan")
+    q[0, 10, 31, 2] = float("inf")
+    rank = torch.rand((1, 32, Q, N), generator=g, device=DEV)
+    rank.masked_fill_(torch.arange(N, device=DEV) > pos[:, None], 2.0)
+    v, lists = rank.sort(dim=-1)
+    lists = torch.where(v[..., :64] < 2.0, lists[..., :64], -1).int().contiguous()
+    hits = _check(keys, q, pos, N, 64, lists)
+    assert hits[0, 0, 20] == 19 and hits[0, 9, 30] == 0  # 21 keys, two without a score; a NaN query
+    assert torch.equal(hits[0, 31, :64], torch.arange(1, 65, device=DEV).int())
