@@ -529,15 +529,17 @@ def run_decode(spec, r, sk, k, steps, warmup, shared=False, attend=True, cpu=Fal
             "peak": PEAK["hbm_GBps"], "unit": "GB/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     # the kernel the library runs for this shape: 16 or more queries per head
-    # take the MFMA kernels (one pass over the codes from 16,384 keys on),
-    # fewer the streaming kernel with 1 or 4 rows per wave
+    # take the MFMA kernels (one pass over the codes from 16,384 keys on), fewer
+    # the decode kernel with 1, 2 or 4 rows of a code set per work-group (up to
+    # three rows over at most 1,024 keys go one by one)
     st = {"f32": 0, "bf16": 1, "fp8": 2}[sk]
     if Q >= 16:
         kern = "score_scan_kernel" if N >= 16384 else "score_batch_kernel"
         inst = f"{kern}<{r}, {st}>"
     else:
         kern = "score_decode_kernel"
-        inst = f"{kern}<{r}, {st}, {4 if (H_q // IH) * Q >= 4 else 1}>"
+        rows = (H_q // IH) * Q
+        inst = f"{kern}<{r}, {st}, {4 if rows > 3 else 1 if N <= 1024 else (1, 2, 4)[rows - 1]}>"
     roof["traffic"] = measured_traffic(kern, spec.name, inst)
     roof["kernel"] = "score_topk"
     roof["work"] = {"bytes": scan_bytes, "code_bytes": code_bytes}

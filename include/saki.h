@@ -268,7 +268,12 @@ int saki_score_topk_noalloc(const void* index, int sketch_dtype, int B, int H_q,
 /* Bytes of the static scratch array behind saki_score_topk_noalloc. */
 size_t saki_noalloc_scratch_bytes(void);
 
-/* Workspace for saki_recall with these sizes (bytes; 0 on bad arguments). */
+/* Workspace for saki_recall with these sizes (bytes; 0 on bad arguments, and
+ * where none is needed).  saki_recall also takes less, down to the partial
+ * lists of a split key axis (for Q < 16; 1,024 bytes per row and chunk, none
+ * for one chunk), and then scores every key in float64 instead of reading the
+ * keys once for all rows of a KV head: the same results, up to 30 times slower
+ * (2^18 keys, 480 rows: 0.3 ms against 9.3 ms).  SAKI_ERR_WORKSPACE below that. */
 size_t saki_recall_workspace_bytes(int B, int H_q, int H_kv, int Q, int N_valid, int d, int k);
 
 /*

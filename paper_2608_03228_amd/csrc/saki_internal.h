@@ -87,10 +87,9 @@ inline Plan make_plan(int B, int heads, int Q, int N_valid, int part_entry_bytes
 // Score path: the workspace holds the partial lists of a split key axis
 // (float score + int index), at least 256 bytes so that a size of 0 keeps
 // meaning invalid arguments.  The MFMA kernels take 16 queries of one head per
-// wave (the one-pass kernel when the rows are long); the decode kernel (whose
-// launch makes the chunks longer, never more)
-// takes the rows of one code set: the H_q / index_heads heads sharing it,
-// times Q.  The two-pass MFMA kernel reads the query sketches z (r values per
+// wave (the one-pass kernel when the rows are long); the decode kernel takes the
+// rows of one code set: the H_q / index_heads heads sharing it, times Q, and its
+// launch makes the chunks longer, never more.  The two-pass MFMA kernel reads the query sketches z (r values per
 // row: bf16 for bf16 and fp8 codes (dtype 1, 2), float32 for float32 codes)
 // at z_off and b = q . mu (one float per row) at b_off, written by a kernel
 // before it; the other kernels form the sketch themselves.
@@ -123,11 +122,6 @@ inline Plan score_plan(int B, int H_q, int index_heads, int Q, int N_valid, int 
     p.z_off = p.n_chunks > 1 ? round_up(rows_total * p.n_chunks * kMaxK * 8, 256) : 0;
     p.b_off = round_up(p.z_off + rows_total * r * (dtype == 0 ? 4 : 2), 256);
     p.ws_bytes = round_up(p.b_off + rows_total * sizeof(float), 256);
-  }
-  const int wave_rows = (int)((H_q / index_heads) * (size_t)Q + p.rows - 1) / p.rows;
-  if (!mfma && wave_rows < 4) {
-    p.waves = 4;
-    p.row_blocks = wave_rows < 1 ? 1 : wave_rows;
   }
   if (p.ws_bytes < 256) p.ws_bytes = 256;
   return p;

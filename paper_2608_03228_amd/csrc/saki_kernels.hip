@@ -2,11 +2,12 @@
 //
 // Kernels (all on the caller's stream):
 //   build_index_kernel   key codes c = B_k^T (k - mu) for every query head (Eq. 4)
-//   append_index_kernel  the same for a few keys
-//   score_batch_kernel   z = B_q^T q, b = q^T mu and s = z . c + b on MFMA for
-//                        blocks of 16 query rows, top-64 per row (two passes:
-//                        block maxima and a threshold, then the candidates)
-//   score_scan_kernel    the same in one pass over the codes for long rows
+//   append_index_kernel  the same for up to 16 keys
+//   query_sketch_kernel  z = B_q^T q and b = q^T mu of many rows
+//   score_batch_kernel   s = z . c + b on MFMA for blocks of 16 query rows,
+//                        top-64 per row (two passes: block maxima and a
+//                        threshold, then the candidates)
+//   score_scan_kernel    z, b and s in one pass over the codes for long rows
 //                        (batches of decode queries), running top-64 per row
 //   score_decode_kernel  the same for few query rows per code set (decode):
 //                        one key per lane, key range split into chunks
@@ -15,9 +16,16 @@
 //   exact_gate_kernel    exact top-64 and recall hits: float32 gate from the
 //                        candidate list, bf16x3 MFMA scan, float64 decisions
 //   exact_bf16_kernel, exact_mfma_kernel  fallback tiers of the same
-//   exact_stream_kernel  exact float64 scores and top-64 for few query rows
+//   exact_tau_kernel, exact_scan_kernel, exact_decide_kernel  the same where few
+//                        query rows share many keys: a gate per row, one bf16x3
+//                        scan of the keys, float64 decisions
+//   exact_stream_kernel  exact float64 scores and top-64, one wave per 1 or 4
+//                        rows: few keys, rows that the scan flags, workspaces
+//                        or alignments that the scan does not take
 //   moments_kernel       calibration moments in float64
-//   attend_kernel        RoPE attention over the selected keys
+//   attend_kernel        RoPE attention over the selected keys, a work-group
+//                        per row
+//   attend_rows_kernel   the same for many rows, a wave per row
 //   export_kernel        debug read-back of the codes
 // Top-k selection is in saki_topk.h.
 
@@ -3504,8 +3512,8 @@ __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per
 
 // ---------------------------------------------------------------- exact scores, keys read once
 
-// Exact top-k and recall hits where few rows share many keys (Q < 16, or a
-// batch too small to fill the GPU with one chunk per row).  What bounds it is
+// Exact top-k and recall hits where few rows share many keys (saki::once_better
+// has the rule).  What bounds it is
 // the key read from HBM, so the rows of all query heads of a KV group share
 // one read: a wave holds 16 of them as MFMA columns (NB times) and streams
 // one chunk of the group's keys.

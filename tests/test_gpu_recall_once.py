@@ -1,4 +1,5 @@
-"""Recall of few rows per key (Q < 16, or batches split over the keys): gates
+"""Recall of few rows per key (Q < 16, or batches split over the keys; fewer keys
+or more rows take the other paths): gates
 from the candidate lists, one scan of the keys for a KV group's rows, float64
 decisions.  Exact sets and hits against float64 numpy."""
 import numpy as np
